@@ -263,7 +263,7 @@ size_t bump(size_t *cur, size_t bytes) {
 }
 
 struct Geometry {
-  int nkb, nd, nchunk, nsplit, kchunk, plane_path, zpair, wide;
+  int nkb, nd, nchunk, nsplit, kchunk, plane_path, zpair, wide, ldb;
   FftDim dx, dy, dz;
   PlaneGeom pg;
   SplitGeom spg;
@@ -394,24 +394,31 @@ void geometry(const qeh_cell *c, const HostMaps &hm, Geometry *g) {
       cur += c->nproj[a];
     }
   }
-  // split-K of beta^H psi: fixed chunks of >= 256 plane waves, enough
-  // workgroups to fill the chip.  Single precision with >= 2048 projectors
-  // and blocks of >= 128 bands takes the wide FP32 tiles (128 bands x 128
-  // projectors, eight waves): at most two rounds of the workgroups resident
-  // at once (256 CUs; one workgroup per CU, two for the Gamma product held to
-  // 128 registers), since a third, nearly empty round costs as much as a full
-  // one; otherwise 64 x 64 tiles (~4 workgroups per CU; measured faster than
-  // 128 x 64 at 128 bands and 512 projectors).
+  // Projector products, split-K of beta^H psi in fixed chunks.
+  // FP64: 64 x 64 tiles, chunks of >= 256 plane waves, ~4 workgroups per CU.
+  // Single precision (split_gemm.hip): 64 x 64 tiles, 64 x 128 at Gamma (its
+  // products do half the MFMA work per staged value), or 128 x 128 ("wide")
+  // with >= 2048 projectors and blocks of >= 128 bands; workgroups for four
+  // rounds of the one resident per CU at 128 x 128, one round of two per CU
+  // otherwise (more splits measured no faster and cost partial sums), chunks
+  // of >= 64 plane waves (four K slices: below that a small cell's product is
+  // the latency of its slices, one after the other).  Rows of the
+  // single-precision beta and psi copy start on 128-byte lines, so that a K
+  // slice of a row is one line: 64 bands x 2048 projectors at Gamma, 74 047
+  // plane waves, 311 us unpadded, 261 us padded.
   g->nsplit = 1;
   g->kchunk = c->npw;
-  g->wide = c->precision == QEH_MIXED && c->block >= 128 && g->nkb >= 2048 ? 1 : 0;
+  const bool f32 = c->precision == QEH_MIXED;
+  g->ldb = f32 ? (c->npw + 15) / 16 * 16 : c->npw;
+  g->wide = f32 && c->block >= 128 && g->nkb >= 2048 ? 1 : 0;
   if (g->nkb > 0) {
     const int bm = g->wide ? 128 : 64;
-    const int bn = g->wide ? 128 : 64;
+    const int bn = g->wide || (f32 && c->gamma) ? 128 : 64;
     const int tiles = ((c->block + bm - 1) / bm) * ((g->nkb + bn - 1) / bn);
-    const int resident = c->gamma ? 2 * 256 : 256;
-    int ns = g->wide ? std::max(1, 2 * resident / tiles) : std::max(1, (1024 + tiles - 1) / tiles);
-    ns = std::min(ns, std::max(1, c->npw / 256));
+    int ns = g->wide ? std::max(1, 4 * 256 / tiles)
+             : f32   ? (2 * 256 + tiles - 1) / tiles
+                     : std::max(1, (1024 + tiles - 1) / tiles);
+    ns = std::min(ns, std::max(1, c->npw / (f32 ? 64 : 256)));
     int kc = (c->npw + ns - 1) / ns;
     kc = (kc + 15) / 16 * 16;
     g->kchunk = kc;
@@ -434,7 +441,7 @@ Layout layout(const qeh_cell *c, const HostMaps &hm, const Geometry &g) {
   L.off_hdiag = bump(&cur, 8 * (size_t)c->npw);
   L.off_vs = bump(&cur, rs * nfft);
   L.off_tw = bump(&cur, cs * (size_t)(c->fft[0] + c->fft[1] + c->fft[2]));
-  L.off_beta = bump(&cur, cs * (size_t)g.nkb * c->npw);
+  L.off_beta = bump(&cur, cs * (size_t)g.nkb * g.ldb);
   L.off_dmat = bump(&cur, 16 * (size_t)g.nd);
   L.off_qmat = bump(&cur, c->qmat ? 16 * (size_t)g.nd : 0);
   L.off_pj0 = bump(&cur, 4 * (size_t)g.nkb);
@@ -448,7 +455,7 @@ Layout layout(const qeh_cell *c, const HostMaps &hm, const Geometry &g) {
                                                c->fft[1]
                                          : 0);
   L.off_colstart = bump(&cur, 4 * (size_t)(hm.ext + 1));
-  L.off_psi32 = bump(&cur, c->precision == QEH_MIXED ? 8 * (size_t)c->block * hm.npw_fft : 0);
+  L.off_psi32 = bump(&cur, c->precision == QEH_MIXED ? 8 * (size_t)c->block * g.ldb : 0);
   // projectors built on the device: the generator's staging area
   L.off_pgen = bump(&cur, g.nkb > 0 && !c->beta ? projgen_layout(c).total : 0);
   // Gamma: the full-sphere H of the band pairs (FP64), written by K3
@@ -550,6 +557,7 @@ qeh_status qeh_ctx_create(const qeh_cell *cell, void *arena, size_t arena_bytes,
   c->zpair = g.zpair;
   c->nsplit = g.nsplit;
   c->wide = g.wide;
+  c->ldb = g.ldb;
   c->kchunk = g.kchunk;
   c->nchunk = g.nchunk;
   c->dx = g.dx;
@@ -715,13 +723,17 @@ qeh_status qeh_ctx_create(const qeh_cell *cell, void *arena, size_t arena_bytes,
     for (size_t i = 0; i < 2 * (size_t)ntw; ++i) f32[i] = (float)tw64[i];
     up(c->d.tw, f32.data(), 4 * f32.size());
     if (e == hipSuccess) e = hipStreamSynchronize(s);
-    // beta in slices of 16M complex to bound the host staging copy
-    const size_t tot = cell->beta ? (size_t)g.nkb * npw : 0, sl = (size_t)1 << 24;
-    for (size_t o = 0; o < tot && e == hipSuccess; o += sl) {
-      const size_t nn = std::min(sl, tot - o);
-      f32.resize(2 * nn);
-      for (size_t i = 0; i < 2 * nn; ++i) f32[i] = (float)cell->beta[2 * o + i];
-      up(reinterpret_cast<char *>(c->d.beta) + 8 * o, f32.data(), 8 * nn);
+    // beta in slices of about 16M complex (whole rows) to bound the host staging copy
+    const int step = (int)std::max<size_t>(1, ((size_t)1 << 24) / g.ldb);
+    for (int r0 = 0; cell->beta && r0 < g.nkb && e == hipSuccess; r0 += step) {
+      const int nr = std::min(step, g.nkb - r0);
+      f32.resize(2 * (size_t)nr * g.ldb);
+      for (int r = 0; r < nr; ++r) {
+        const double *src = cell->beta + 2 * (size_t)(r0 + r) * npw;
+        float *dst = f32.data() + 2 * (size_t)r * g.ldb;
+        for (size_t i = 0; i < 2 * (size_t)npw; ++i) dst[i] = (float)src[i];
+      }
+      up(reinterpret_cast<float2 *>(c->d.beta) + (size_t)r0 * g.ldb, f32.data(), 4 * f32.size());
       if (e == hipSuccess) e = hipStreamSynchronize(s);
     }
   }
@@ -732,7 +744,7 @@ qeh_status qeh_ctx_create(const qeh_cell *cell, void *arena, size_t arena_bytes,
   }
   if (g.nkb > 0 && !cell->beta) {
     // beta (context precision) and the nonlocal part of diag(H) on the device
-    const qeh_status pst = projgen_run(cell, f64, c->d.beta, npw, A + L.off_pgen, s, c->d.dmat,
+    const qeh_status pst = projgen_run(cell, f64, c->d.beta, c->ldb, A + L.off_pgen, s, c->d.dmat,
                                        c->d.hdiag);
     if (pst != QEH_OK) {
       delete c;
@@ -830,11 +842,11 @@ qeh_status apply_block(qeh_ctx *c, int part, int nbk, const double2 *psi, int ld
     // K1 has just written psi32 (the single-precision copy of the block)
     const bool use32 = !f64 && part == 2;
     g1.A = use32 ? static_cast<const void *>(c->d.psi32) : static_cast<const void *>(psi);
-    g1.lda = use32 ? c->npw_fft : ldpsi;
+    g1.lda = use32 ? c->ldb : ldpsi;
     g1.ta = use32 ? T_F2 : T_D2;
-    g1.tile = c->wide;
+    g1.tile = c->wide ? 2 : c->gamma ? 1 : 0;
     g1.B = c->d.beta;
-    g1.ldb = c->npw;
+    g1.ldb = c->ldb;
     g1.tb = f64 ? T_D2 : T_F2;
     g1.bmode = 0;
     g1.C = c->d.part;
@@ -847,11 +859,10 @@ qeh_status apply_block(qeh_ctx *c, int part, int nbk, const double2 *psi, int ld
     g1.nsplit = c->nsplit;
     g1.kchunk = c->kchunk;
     g1.split_stride = (long)c->block * c->nkb;
-    g1.prec = f64 ? G_F64 : G_F32;
     g1.rmode = c->gamma ? 1 : 0;   // Gamma: only the real part enters becp
     {
       StageGuard g(c, 3);
-      e = launch_cgemm(g1, c->stream);
+      e = f64 ? launch_cgemm(g1, c->stream) : launch_split_gemm(g1, c->stream);
     }
     if (e != hipSuccess) return hip_fail(e, "beta^H psi launch");
     {
@@ -864,7 +875,7 @@ qeh_status apply_block(qeh_ctx *c, int part, int nbk, const double2 *psi, int ld
     g3.lda = c->nkb;
     g3.ta = f64 ? T_D2 : c->gamma ? T_F1 : T_F2;   // single-precision Gamma: real ps
     g3.B = c->d.beta;
-    g3.ldb = c->npw;
+    g3.ldb = c->ldb;
     g3.tb = f64 ? T_D2 : T_F2;
     g3.bmode = 1;
     g3.C = hpsi;
@@ -876,12 +887,11 @@ qeh_status apply_block(qeh_ctx *c, int part, int nbk, const double2 *psi, int ld
     g3.accumulate = part == 2 ? 1 : 0;
     g3.nsplit = 1;
     g3.kchunk = c->nkb;
-    g3.prec = f64 ? G_F64 : G_F32;
     g3.rmode = c->gamma ? 2 : 0;   // Gamma: ps is real
-    g3.tile = c->wide;
+    g3.tile = c->wide ? 2 : 0;
     {
       StageGuard g(c, 5);
-      e = launch_cgemm(g3, c->stream);
+      e = f64 ? launch_cgemm(g3, c->stream) : launch_split_gemm(g3, c->stream);
     }
     if (e != hipSuccess) return hip_fail(e, "beta ps launch");
   } else if (part == 1) {
@@ -938,7 +948,7 @@ qeh_status apply_s_impl(qeh_ctx *c, int nb, const double *psi, int ldpsi, double
     g1.lda = ldpsi;
     g1.ta = T_D2;
     g1.B = c->d.beta;
-    g1.ldb = c->npw;
+    g1.ldb = c->ldb;
     g1.tb = f64 ? T_D2 : T_F2;
     g1.bmode = 0;
     g1.C = c->d.part;
@@ -951,10 +961,9 @@ qeh_status apply_s_impl(qeh_ctx *c, int nb, const double *psi, int ldpsi, double
     g1.nsplit = c->nsplit;
     g1.kchunk = c->kchunk;
     g1.split_stride = (long)c->block * c->nkb;
-    g1.prec = f64 ? G_F64 : G_F32;
     g1.rmode = c->gamma ? 1 : 0;
-    g1.tile = c->wide;
-    e = launch_cgemm(g1, c->stream);
+    g1.tile = c->wide ? 2 : c->gamma ? 1 : 0;
+    e = f64 ? launch_cgemm(g1, c->stream) : launch_split_gemm(g1, c->stream);
     if (e == hipSuccess) e = launch_dscale(c, nbk, pb, ldpsi, c->d.qmat);
     if (e != hipSuccess) return hip_fail(e, "S psi projections");
     GemmDesc g3{};
@@ -962,7 +971,7 @@ qeh_status apply_s_impl(qeh_ctx *c, int nb, const double *psi, int ldpsi, double
     g3.lda = c->nkb;
     g3.ta = f64 ? T_D2 : c->gamma ? T_F1 : T_F2;   // single-precision Gamma: real ps
     g3.B = c->d.beta;
-    g3.ldb = c->npw;
+    g3.ldb = c->ldb;
     g3.tb = f64 ? T_D2 : T_F2;
     g3.bmode = 1;
     g3.C = o + (size_t)b0 * ldsp;
@@ -974,10 +983,9 @@ qeh_status apply_s_impl(qeh_ctx *c, int nb, const double *psi, int ldpsi, double
     g3.accumulate = 1;
     g3.nsplit = 1;
     g3.kchunk = c->nkb;
-    g3.prec = f64 ? G_F64 : G_F32;
     g3.rmode = c->gamma ? 2 : 0;
-    g3.tile = c->wide;
-    e = launch_cgemm(g3, c->stream);
+    g3.tile = c->wide ? 2 : 0;
+    e = f64 ? launch_cgemm(g3, c->stream) : launch_split_gemm(g3, c->stream);
     if (e != hipSuccess) return hip_fail(e, "S psi product");
   }
   return QEH_OK;

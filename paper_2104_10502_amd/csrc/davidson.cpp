@@ -117,7 +117,6 @@ hipError_t reduce_cols(const qeh_ctx *c, const double2 *X, int nrow, const doubl
   g.M = ncol;
   g.N = nrow;
   g.K = c->npw;
-  g.prec = G_F64;
   hipError_t e;
   if (ns == 1) {
     g.C = out;
@@ -164,7 +163,6 @@ hipError_t square_product(const qeh_ctx *c, const double2 *Qm, const double2 *Pm
   g.K = n;
   g.nsplit = 1;
   g.kchunk = n;
-  g.prec = G_F64;
   return launch_cgemm(g, c->stream);
 }
 
@@ -187,7 +185,6 @@ hipError_t square_product_cols(const qeh_ctx *c, const double2 *Qm, const double
   g.K = n;
   g.nsplit = 1;
   g.kchunk = n;
-  g.prec = G_F64;
   return launch_cgemm(g, c->stream);
 }
 
@@ -210,7 +207,6 @@ hipError_t rotate(const qeh_ctx *c, const double2 *Y, int ld, int n, int nb, con
   g.K = n;
   g.nsplit = 1;
   g.kchunk = n;
-  g.prec = G_F64;
   return launch_cgemm(g, c->stream);
 }
 

@@ -1209,7 +1209,7 @@ hipError_t k1_impl(const qeh_ctx *c, int nbk, const double2 *psi, int ldpsi, int
   hipLaunchKernelGGL((k1_scatter_zinv<C, GAM>), grid, dim3(kNT), c->sg.lds_bytes, c->stream,
                      psi, ldpsi, reinterpret_cast<C *>(c->d.sbuf), c->d.stick_off, c->d.gmap, tw,
                      c->dz, c->nst, c->sg.S, c->sg.ldz, c->sg.s_div, c->sg.slast_div,
-                     p32, c->npw_fft, nb_gam, c->npw, pairs);
+                     p32, c->ldb, nb_gam, c->npw, pairs);
   return hipGetLastError();
 }
 
@@ -1369,7 +1369,7 @@ hipError_t k1_pair_launch(const qeh_ctx *c, int nbk, const double2 *psi, int ldp
   allow_lds(k1_pair<N, GAM>, lds);
   hipLaunchKernelGGL((k1_pair<N, GAM>), dim3((c->nst + kPairSticks - 1) / kPairSticks, nbk),
                      dim3(kNT), lds, c->stream, psi, ldpsi, reinterpret_cast<float2 *>(c->d.sbuf),
-                     c->d.stick_off, c->d.gmap, c->nst, p32, c->npw_fft, nb_gam, c->npw,
+                     c->d.stick_off, c->d.gmap, c->nst, p32, c->ldb, nb_gam, c->npw,
                      pairs);
   return hipGetLastError();
 }

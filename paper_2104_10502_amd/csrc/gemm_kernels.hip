@@ -1,5 +1,5 @@
-// Complex matrix products on the MFMA units, and the D scaling of the
-// projector coefficients.
+// FP64 complex matrix products on the MFMA units, and the D scaling of the
+// projector coefficients (the single-precision products: split_gemm.hip).
 //
 // Uses: the pseudopotential contribution of H (becp = beta^H psi, ps = D becp,
 // hpsi += beta ps), which the paper lists among the ported Hamiltonian
@@ -14,8 +14,8 @@
 // The operand sums are formed in registers after the LDS reads.  The form is
 // normwise stable; its rounding error is a small constant multiple of that of
 // the four-product form (Cr = Ar Br - Ai Bi, Ci = Ar Bi + Ai Br), and it issues
-// a quarter fewer MFMAs.  The FP64 instances are held to three waves per SIMD
-// (their third accumulator set would otherwise push them to two).
+// a quarter fewer MFMAs.  The kernels are held to three waves per SIMD (the
+// third accumulator set would otherwise push them to two).
 // Two cheaper forms serve the Gamma-point projections (RM = 1: only the real
 // part of C is wanted, Cr = P1 - P2; RM = 2: A is real, Cr = sum Ar Br and
 // Ci = sum Ar Bi): two MFMA products per step instead of three.
@@ -31,85 +31,31 @@
 namespace qeh {
 namespace {
 
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 
-// Accumulator of one BS x BS block: BS = 16 (f32 or f64, k = 4 per
-// instruction) or 32 (f32 only, k = 2 per instruction; on this chip the
-// 32 x 32 f32 instruction sustains close to the matrix peak, the 16 x 16 one
-// about 0.85 of it).
-template <typename R, int BS> struct acc_of;
-template <> struct acc_of<float, 16> { using type = floatx4; };
-template <> struct acc_of<float, 32> { using type = floatx16; };
-template <> struct acc_of<double, 16> { using type = doublex4; };
-
-__device__ __forceinline__ void mfma(float a, float b, floatx4 &c) {
-  c = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-__device__ __forceinline__ void mfma(float a, float b, floatx16 &c) {
-  c = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
-}
 __device__ __forceinline__ void mfma(double a, double b, doublex4 &c) {
   c = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-// Operand load: element of type T (double2/float2) -> compute type R, conj.
-template <typename R, typename T>
-__device__ __forceinline__ void ld_elem(const T *p, bool valid, bool cj, R &re, R &im) {
-  if (valid) {
-    const T v = *p;
-    re = static_cast<R>(v.x);
-    im = cj ? -static_cast<R>(v.y) : static_cast<R>(v.y);
-  } else {
-    re = R(0);
-    im = R(0);
-  }
-}
-
-template <typename T> __device__ __forceinline__ T zero_of() {
-  T z;
-  z.x = 0;
-  z.y = 0;
-  return z;
-}
-template <> __device__ __forceinline__ float zero_of<float>() { return 0.f; }
-
-// real and imaginary parts of an operand element (a real element: imaginary 0)
-template <typename R, typename T> __device__ __forceinline__ R re_of(const T &v) {
-  return static_cast<R>(v.x);
-}
-template <typename R, typename T> __device__ __forceinline__ R im_of(const T &v) {
-  return static_cast<R>(v.y);
-}
-template <> __device__ __forceinline__ float re_of<float, float>(const float &v) { return v; }
-template <> __device__ __forceinline__ float im_of<float, float>(const float &v) { return 0.f; }
-
 // One workgroup: a BM x BN tile of C over the K slice [kbeg, kend).  Global
 // tiles are prefetched into registers while the MFMAs consume the LDS copy of
 // the previous slice (two LDS buffers, one barrier per slice).
-template <typename R, typename TA, typename TB, typename TC, int BMODE, int BM, int BN, int BK,
-          int RM, int WGM, int WGN, int BS, int WPE>
-__global__ __launch_bounds__(64 * WGM * WGN)
-__attribute__((amdgpu_waves_per_eu(WPE > 0 ? WPE : (sizeof(R) == 8 ? 3 : 1))))
+template <int BMODE, int BM, int BN, int BK, int RM, int WGM, int WGN>
+__global__ __launch_bounds__(64 * WGM * WGN) __attribute__((amdgpu_waves_per_eu(3)))
 void cgemm_kernel(
-    const TA *__restrict__ A, long lda, const TB *__restrict__ B, long ldb, TC *__restrict__ C,
-    long ldc, int M, int N, int K, int conjA, int conjB, int accumulate, int kchunk,
-    long split_stride, int tiles_m, int tiles_n, int ntiles, int per_xcd) {
-  using ACC = typename acc_of<R, BS>::type;
-  constexpr int NACC = BS * BS / 64;   // accumulator entries per lane
-  constexpr int KS = BS == 32 ? 2 : 4;   // k per instruction
-  static_assert(BK % KS == 0, "K slice / instruction k mismatch");
+    const double2 *__restrict__ A, long lda, const double2 *__restrict__ B, long ldb,
+    double2 *__restrict__ C, long ldc, int M, int N, int K, int conjA, int conjB, int accumulate,
+    int kchunk, long split_stride, int tiles_m, int tiles_n, int ntiles, int per_xcd) {
   constexpr int kGT = 64 * WGM * WGN;
   constexpr int BKP = BK + 1;
-  constexpr int TM = BM / (BS * WGM);
-  constexpr int TN = BN / (BS * WGN);
+  constexpr int TM = BM / (16 * WGM);
+  constexpr int TN = BN / (16 * WGN);
   constexpr int NA = BM * BK / kGT;
   constexpr int NB = BN * BK / kGT;
-  static_assert(TM * BS * WGM == BM && TN * BS * WGN == BN, "tile / wave mismatch");
+  static_assert(TM * 16 * WGM == BM && TN * 16 * WGN == BN && BK % 4 == 0, "tile / wave mismatch");
   static_assert(NA * kGT == BM * BK && NB * kGT == BN * BK, "tile / thread mismatch");
-  __shared__ R As[2][2][BM * BKP];   // [buffer][re, im]
-  __shared__ R Bs[2][2][BN * BKP];
+  __shared__ double As[2][2][BM * BKP];   // [buffer][re, im]
+  __shared__ double Bs[2][2][BN * BKP];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -130,86 +76,76 @@ void cgemm_kernel(
   const int n0 = nt * BN;
   const int kbeg = kz * kchunk;
   const int kend = min(K, kbeg + kchunk);
-  TC *Cz = C + (long)kz * split_stride;
-  const R sa = conjA ? R(-1) : R(1);
-  const R sb = conjB ? R(-1) : R(1);
+  double2 *Cz = C + (long)kz * split_stride;
+  const double sa = conjA ? -1.0 : 1.0;
+  const double sb = conjB ? -1.0 : 1.0;
 
-  ACC p1[TM][TN], p2[TM][TN], p3[TM][TN];
+  doublex4 p1[TM][TN], p2[TM][TN], p3[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int e = 0; e < NACC; ++e) {
-        p1[i][j][e] = R(0);
-        p2[i][j][e] = R(0);
-        p3[i][j][e] = R(0);
+      for (int e = 0; e < 4; ++e) {
+        p1[i][j][e] = 0.0;
+        p2[i][j][e] = 0.0;
+        p3[i][j][e] = 0.0;
       }
 
   // Global operand loads for one K slice into registers.
-  auto gload = [&](int k0, TA *ra, TB *rb) {
+  auto gload = [&](int k0, double2 *ra, double2 *rb) {
 #pragma unroll
     for (int u = 0; u < NA; ++u) {
       const int e = tid + u * kGT;
       const int r = e / BK, k = e % BK;
       const int gm = m0 + r, gk = k0 + k;
-      ra[u] = (gm < M && gk < kend) ? A[(long)gm * lda + gk] : zero_of<TA>();
+      ra[u] = (gm < M && gk < kend) ? A[(long)gm * lda + gk] : make_double2(0.0, 0.0);
     }
 #pragma unroll
     for (int u = 0; u < NB; ++u) {
       const int e = tid + u * kGT;
-      if (BMODE == 0) {
-        const int r = e / BK, k = e % BK;
-        const int gn = n0 + r, gk = k0 + k;
-        rb[u] = (gn < N && gk < kend) ? B[(long)gn * ldb + gk] : zero_of<TB>();
-      } else {
-        const int k = e / BN, r = e % BN;
-        const int gn = n0 + r, gk = k0 + k;
-        rb[u] = (gn < N && gk < kend) ? B[(long)gk * ldb + gn] : zero_of<TB>();
-      }
+      const int k = BMODE == 0 ? e % BK : e / BN;
+      const int r = BMODE == 0 ? e / BK : e % BN;
+      const int gn = n0 + r, gk = k0 + k;
+      const long at = BMODE == 0 ? (long)gn * ldb + gk : (long)gk * ldb + gn;
+      rb[u] = (gn < N && gk < kend) ? B[at] : make_double2(0.0, 0.0);
     }
   };
-  auto sstore = [&](int buf, const TA *ra, const TB *rb) {
+  auto sstore = [&](int buf, const double2 *ra, const double2 *rb) {
 #pragma unroll
     for (int u = 0; u < NA; ++u) {
       const int e = tid + u * kGT;
       const int r = e / BK, k = e % BK;
-      As[buf][0][r * BKP + k] = re_of<R>(ra[u]);
-      As[buf][1][r * BKP + k] = sa * im_of<R>(ra[u]);
+      As[buf][0][r * BKP + k] = ra[u].x;
+      As[buf][1][r * BKP + k] = sa * ra[u].y;
     }
 #pragma unroll
     for (int u = 0; u < NB; ++u) {
       const int e = tid + u * kGT;
-      int r, k;
-      if (BMODE == 0) {
-        r = e / BK;
-        k = e % BK;
-      } else {
-        k = e / BN;
-        r = e % BN;
-      }
-      Bs[buf][0][r * BKP + k] = static_cast<R>(rb[u].x);
-      Bs[buf][1][r * BKP + k] = sb * static_cast<R>(rb[u].y);
+      const int k = BMODE == 0 ? e % BK : e / BN;
+      const int r = BMODE == 0 ? e / BK : e % BN;
+      Bs[buf][0][r * BKP + k] = rb[u].x;
+      Bs[buf][1][r * BKP + k] = sb * rb[u].y;
     }
   };
 
-  const int lr = lane % BS;   // row (A) / column (B) inside a block
-  const int lk = lane / BS;   // k inside a step of KS
+  const int lr = lane % 16;   // row (A) / column (B) inside a block
+  const int lk = lane / 16;   // k inside a step of 4
 
   auto compute = [&](int buf) {
 #pragma unroll
-    for (int kk = 0; kk < BK; kk += KS) {
-      R ar[TM], ai[TM], as[TM], br[TN], bi[TN], bs[TN];
+    for (int kk = 0; kk < BK; kk += 4) {
+      double ar[TM], ai[TM], as[TM], br[TN], bi[TN], bs[TN];
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
-        const int off = (wm0 + i * BS + lr) * BKP + kk + lk;
+        const int off = (wm0 + i * 16 + lr) * BKP + kk + lk;
         ar[i] = As[buf][0][off];
         ai[i] = As[buf][1][off];
         as[i] = ar[i] + ai[i];
       }
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
-        const int off = (wn0 + j * BS + lr) * BKP + kk + lk;
+        const int off = (wn0 + j * 16 + lr) * BKP + kk + lk;
         br[j] = Bs[buf][0][off];
         bi[j] = Bs[buf][1][off];
         bs[j] = br[j] + bi[j];
@@ -230,8 +166,7 @@ void cgemm_kernel(
   };
 
   // one slice in flight: loaded during the MFMAs of the previous one
-  TA ra[NA];
-  TB rb[NB];
+  double2 ra[NA], rb[NB];
   if (kbeg < kend) {
     gload(kbeg, ra, rb);
     sstore(0, ra, rb);
@@ -247,75 +182,46 @@ void cgemm_kernel(
     buf ^= 1;
   }
 
-  // ---- epilogue.  Column lane%BS of each block.  16 x 16 blocks:
-  // accumulator entry r holds row 4*(lane/16)+r for the f32 instruction but
-  // row lane/16+4*r for the f64 one (the two lay out D differently); 32 x 32
-  // f32 blocks: entry r holds row (r%4) + 8*(r/4) + 4*(lane/32).
-  constexpr bool kF64 = sizeof(R) == 8;
+  // ---- epilogue.  Column lane%16 of each block; accumulator entry r holds
+  // row lane/16+4*r (the f32 instructions lay out D differently).
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int r = 0; r < NACC; ++r) {
-        const int rw = BS == 32 ? (r % 4) + 8 * (r / 4) + 4 * lk : kF64 ? lk + 4 * r : 4 * lk + r;
-        const int gm = m0 + wm0 + i * BS + rw;
-        const int gn = n0 + wn0 + j * BS + lr;
+      for (int r = 0; r < 4; ++r) {
+        const int gm = m0 + wm0 + i * 16 + lk + 4 * r;
+        const int gn = n0 + wn0 + j * 16 + lr;
         if (gm < M && gn < N) {
-          TC *p = Cz + (long)gm * ldc + gn;
-          using RC = typename real_of<TC>::type;
-          const R cr = RM == 2 ? p1[i][j][r] : p1[i][j][r] - p2[i][j][r];
-          const R ci = RM == 0   ? p3[i][j][r] - p1[i][j][r] - p2[i][j][r]
-                       : RM == 2 ? p2[i][j][r]
-                                 : R(0);
+          double2 *p = Cz + (long)gm * ldc + gn;
+          double cr = RM == 2 ? p1[i][j][r] : p1[i][j][r] - p2[i][j][r];
+          double ci = RM == 0   ? p3[i][j][r] - p1[i][j][r] - p2[i][j][r]
+                      : RM == 2 ? p2[i][j][r]
+                                : 0.0;
           if (accumulate) {
-            TC v = *p;
-            // the add happens in the result's precision
-            v.x = v.x + static_cast<RC>(cr);
-            v.y = v.y + static_cast<RC>(ci);
-            *p = v;
-          } else {
-            TC v;
-            v.x = static_cast<RC>(cr);
-            v.y = static_cast<RC>(ci);
-            *p = v;
+            const double2 v = *p;
+            cr += v.x;
+            ci += v.y;
           }
+          *p = make_double2(cr, ci);
         }
       }
 }
 
-template <typename R, typename TA, typename TB, typename TC, int BMODE, int BM, int BN, int BK,
-          int RM = 0, int WGM = 2, int WGN = 2, int BS = 16, int WPE = 0>
-hipError_t run_tile(const GemmDesc &g, hipStream_t s) {
+// 64 x 64 tiles on four waves, K slices of 8.
+template <int BMODE, int RM> hipError_t run_tile(const GemmDesc &g, hipStream_t s) {
+  constexpr int BM = 64, BN = 64;
   const int tm = (g.M + BM - 1) / BM, tn = (g.N + BN - 1) / BN;
   const long total = (long)tm * tn * g.nsplit;
   if (total > (1L << 30)) return hipErrorInvalidValue;
   const int per_xcd = (int)((total + 7) / 8);
   const int kchunk = g.nsplit > 1 ? g.kchunk : g.K;
-  hipLaunchKernelGGL((cgemm_kernel<R, TA, TB, TC, BMODE, BM, BN, BK, RM, WGM, WGN, BS, WPE>),
-                     dim3(8 * per_xcd), dim3(64 * WGM * WGN), 0, s, reinterpret_cast<const TA *>(g.A), g.lda,
-                     reinterpret_cast<const TB *>(g.B), g.ldb, reinterpret_cast<TC *>(g.C), g.ldc,
-                     g.M, g.N, g.K, g.conjA, g.conjB, g.accumulate, kchunk, g.split_stride, tm, tn,
-                     (int)total, per_xcd);
+  hipLaunchKernelGGL((cgemm_kernel<BMODE, BM, BN, 8, RM, 2, 2>), dim3(8 * per_xcd), dim3(256), 0,
+                     s, reinterpret_cast<const double2 *>(g.A), g.lda,
+                     reinterpret_cast<const double2 *>(g.B), g.ldb,
+                     reinterpret_cast<double2 *>(g.C), g.ldc, g.M, g.N, g.K, g.conjA, g.conjB,
+                     g.accumulate, kchunk, g.split_stride, tm, tn, (int)total, per_xcd);
   return hipGetLastError();
-}
-
-// FP64: 64 x 64 tiles, K slices of 8 (16 x 16 blocks).  FP32: 64 x 64 tiles
-// on four waves (16 x 16 blocks), or the wide tile for the large projector
-// products: 128 x 128 on eight waves with 32 x 32 blocks (half the operand
-// re-reads of 64 x 64, and the faster 32 x 32 instruction).
-template <typename TA, typename TC, int BMODE>
-hipError_t run_f32(const GemmDesc &g, hipStream_t s) {
-  if (g.tile == 1) return run_tile<float, TA, float2, TC, BMODE, 128, 128, 16, 0, 2, 4, 32>(g, s);
-  return run_tile<float, TA, float2, TC, BMODE, 64, 64, 16>(g, s);
-}
-
-template <typename TA, typename TC> hipError_t run_f32_b(const GemmDesc &g, hipStream_t s) {
-  return g.bmode == 0 ? run_f32<TA, TC, 0>(g, s) : run_f32<TA, TC, 1>(g, s);
-}
-
-template <typename TA> hipError_t run_f32_c(const GemmDesc &g, hipStream_t s) {
-  return g.tc == T_D2 ? run_f32_b<TA, double2>(g, s) : run_f32_b<TA, float2>(g, s);
 }
 
 template <typename TP, typename TC>
@@ -430,53 +336,15 @@ __global__ __launch_bounds__(256) void dscale_kernel(
 
 }  // namespace
 
-// The Gamma-point forms: RM = 1 for beta^H psi (bmode 0, psi read in double,
-// or its single-precision copy), RM = 2 for beta ps (bmode 1, A = ps real:
-// complex storage in FP64, one float per entry in single precision;
-// C = hpsi).  FP32 wide tiles (tile 1): beta^H psi from the single-precision
-// copy on 128 x 128 held to 128 registers (four waves per SIMD, two
-// workgroups per CU: 2.54 against 2.72 ms for 128 x 256 at the 512-atom
-// cell), from psi in double on 128 x 256 (psi re-read once per 256
-// projectors); beta ps on 128 x 128.
-hipError_t launch_cgemm_real(const GemmDesc &g, hipStream_t s) {
-  if (g.prec == G_F64) {
-    if (g.ta != T_D2 || g.tb != T_D2 || g.tc != T_D2) return hipErrorInvalidValue;
-    if (g.rmode == 1 && g.bmode == 0)
-      return run_tile<double, double2, double2, double2, 0, 64, 64, 8, 1>(g, s);
-    if (g.rmode == 2 && g.bmode == 1)
-      return run_tile<double, double2, double2, double2, 1, 64, 64, 8, 2>(g, s);
-    return hipErrorInvalidValue;
-  }
-  if (g.tb != T_F2) return hipErrorInvalidValue;
-  if (g.rmode == 1 && g.bmode == 0 && g.ta == T_D2 && g.tc == T_F2)
-    return g.tile == 1
-               ? run_tile<float, double2, float2, float2, 0, 128, 256, 16, 1, 2, 4, 32>(g, s)
-               : run_tile<float, double2, float2, float2, 0, 64, 64, 16, 1>(g, s);
-  if (g.rmode == 1 && g.bmode == 0 && g.ta == T_F2 && g.tc == T_F2)
-    return g.tile == 1
-               ? run_tile<float, float2, float2, float2, 0, 128, 128, 16, 1, 2, 4, 32, 4>(g, s)
-               : run_tile<float, float2, float2, float2, 0, 64, 64, 16, 1>(g, s);
-  if (g.rmode == 2 && g.bmode == 1 && g.ta == T_F2 && g.tc == T_D2)
-    return g.tile == 1
-               ? run_tile<float, float2, float2, double2, 1, 128, 128, 16, 2, 2, 4, 32>(g, s)
-               : run_tile<float, float2, float2, double2, 1, 64, 64, 16, 2>(g, s);
-  if (g.rmode == 2 && g.bmode == 1 && g.ta == T_F1 && g.tc == T_D2)
-    return g.tile == 1
-               ? run_tile<float, float, float2, double2, 1, 128, 128, 16, 2, 2, 4, 32>(g, s)
-               : run_tile<float, float, float2, double2, 1, 64, 64, 16, 2>(g, s);
-  return hipErrorInvalidValue;
-}
-
+// The Gamma-point forms: RM = 1 for beta^H psi (bmode 0), RM = 2 for beta ps
+// (bmode 1, A = ps real in complex storage).
 hipError_t launch_cgemm(const GemmDesc &g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0 || g.K <= 0) return hipSuccess;
-  if (g.rmode != 0) return launch_cgemm_real(g, s);
-  if (g.prec == G_F64) {
-    if (g.ta != T_D2 || g.tb != T_D2 || g.tc != T_D2) return hipErrorInvalidValue;
-    return g.bmode == 0 ? run_tile<double, double2, double2, double2, 0, 64, 64, 8>(g, s)
-                        : run_tile<double, double2, double2, double2, 1, 64, 64, 8>(g, s);
-  }
-  if (g.tb != T_F2) return hipErrorInvalidValue;
-  return g.ta == T_D2 ? run_f32_c<double2>(g, s) : run_f32_c<float2>(g, s);
+  if (g.ta != T_D2 || g.tb != T_D2 || g.tc != T_D2) return hipErrorInvalidValue;
+  if (g.rmode == 0) return g.bmode == 0 ? run_tile<0, 0>(g, s) : run_tile<1, 0>(g, s);
+  if (g.rmode == 1 && g.bmode == 0) return run_tile<0, 1>(g, s);
+  if (g.rmode == 2 && g.bmode == 1) return run_tile<1, 2>(g, s);
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_splitk_reduce(const void *part, int tp, long stride, int nsplit, int M, int N,
@@ -507,20 +375,20 @@ hipError_t launch_dscale(const qeh_ctx *c, int nbk, const double2 *psi, long ldp
                        reinterpret_cast<const double2 *>(c->d.part), ss, c->nsplit, c->nkb,
                        reinterpret_cast<double2 *>(c->d.ps), mat, c->d.pj0, c->d.pnb,
                        c->d.pdoff, c->d.chunk, gpsi, ldpsi,
-                       reinterpret_cast<const double2 *>(c->d.beta), (long)c->npw);
+                       reinterpret_cast<const double2 *>(c->d.beta), (long)c->ldb);
   } else if (c->gamma) {
     // real ps, one float per entry: half the A operand of the beta ps product
     hipLaunchKernelGGL((dscale_kernel<float2, float>), grid, dim3(256), 0, c->stream,
                        reinterpret_cast<const float2 *>(c->d.part), ss, c->nsplit, c->nkb,
                        reinterpret_cast<float *>(c->d.ps), mat, c->d.pj0, c->d.pnb,
                        c->d.pdoff, c->d.chunk, gpsi, ldpsi,
-                       reinterpret_cast<const float2 *>(c->d.beta), (long)c->npw);
+                       reinterpret_cast<const float2 *>(c->d.beta), (long)c->ldb);
   } else {
     hipLaunchKernelGGL((dscale_kernel<float2, float2>), grid, dim3(256), 0, c->stream,
                        reinterpret_cast<const float2 *>(c->d.part), ss, c->nsplit, c->nkb,
                        reinterpret_cast<float2 *>(c->d.ps), mat, c->d.pj0, c->d.pnb,
                        c->d.pdoff, c->d.chunk, gpsi, ldpsi,
-                       reinterpret_cast<const float2 *>(c->d.beta), (long)c->npw);
+                       reinterpret_cast<const float2 *>(c->d.beta), (long)c->ldb);
   }
   return hipGetLastError();
 }

@@ -80,7 +80,7 @@ struct DevMaps {
   double *hdiag;     // [npw] diag(H)
   void *vs;          // [N3][N2][N1] V/N (double or float)
   void *tw;          // twiddles x | y | z (double2 or float2)
-  void *beta;        // [nkb][npw] (double2 or float2)
+  void *beta;        // [nkb][ldb] (double2 or float2)
   double2 *dmat;     // concatenated blocks
   double2 *qmat;     // overlap q blocks (same layout), or null
   int *pj0;          // [nkb] first projector of the atom block of i
@@ -91,7 +91,7 @@ struct DevMaps {
   void *part;        // [nsplit][block][nkb] split-K partials
   void *ps;          // [block][nkb] D * becp (working complex type; real floats on
                      // single-precision Gamma contexts)
-  float2 *psi32;     // mixed form: [block][npw] single-precision copy of psi (K1)
+  float2 *psi32;     // mixed form: [block][ldb] single-precision copy of psi (K1)
   void *big;         // split plane path: [block][N3][ext][N2] (or null)
   double2 *gbuf;     // Gamma: [(block+1)/2][npw_fft] full-sphere H of band pairs (or null)
   int *colstart;     // [ext+1] first stick of each x-extent column
@@ -110,7 +110,9 @@ struct qeh_ctx {
                         // 4 lane-quad kernel (FP64)
   int zpair = 0;        // 1: lane-pair K1 / K3 (gmap at natural z)
   int nsplit = 1, kchunk = 0;
-  int wide = 0;         // 1: wide FP32 tiles for the projector products
+  int wide = 0;         // 1: wide single-precision tiles for the projector products
+  int ldb = 0;          // row length of beta and psi32 (npw; single precision: padded to
+                        // whole 128-byte lines)
   int nchunk = 0;
   qeh::FftDim dx{}, dy{}, dz{};
   qeh::PlaneGeom pg{};
@@ -219,7 +221,6 @@ hipError_t beta_static_scratch(hipStream_t s, char **out);
 //      bmode 1: element (k,n) at B[k*ldb + n].
 //   Split-K: grid z = nsplit slices of kchunk; slice s writes
 //      C + s*split_stride (accumulate must be 0 then).
-enum GemmPrec { G_F64 = 0, G_F32 = 1 };
 enum GemmType { T_D2 = 0, T_F2 = 1, T_F1 = 2 };   // operand storage (T_F1: real float)
 struct GemmDesc {
   const void *A; long lda; int ta;
@@ -228,11 +229,15 @@ struct GemmDesc {
   int M, N, K;
   int conjA, conjB, accumulate;
   int nsplit, kchunk; long split_stride;
-  int prec;
-  int tile;   // FP32 tiles: 0 = 64 x 64; 1 = wide (128 x 128, Gamma beta^H psi 128 x 256)
+  int tile;   // launch_split_gemm: 0 = 64 x 64, 1 = 64 x 128, 2 = 128 x 128
   int rmode;  // 0 complex; 1 only Re(C) wanted (Im written 0); 2 A real (Im A ignored)
 };
+// FP64 operands and results.
 hipError_t launch_cgemm(const GemmDesc &g, hipStream_t s);
+// The single-precision projector products: B and the products in single
+// precision, beta^H psi (bmode 0, conjB; A in float or double, C float) and
+// beta ps (bmode 1; C double).
+hipError_t launch_split_gemm(const GemmDesc &g, hipStream_t s);
 
 // ---- Davidson building blocks shared with the CG solver (davidson.cpp) ----
 // out(i, j) = <X_i|Y_j> for i < nrow, j < ncol (col-major, ld), FP64 MFMA,
