@@ -488,23 +488,23 @@ qeh_status qeh_server_stats(qeh_server *srv, double *out, int n);
 qeh_status qeh_server_destroy(qeh_server *srv);
 
 /* Shape facts of a context: [npw, nst, nkb, N1, N2, N3, x-extent, block,
- * precision, plane path (0 fused in one kernel, 1 split through HBM,
- * 2 lane-pair register kernel, 4 lane-quad register kernel), stick path
- * (0 LDS passes, 1 lane-pair register z transforms), projector tiles (0 the
- * 64 x 64 MFMA tiles, 1 the wide single-precision tiles: QEH_MIXED with
- * >= 2048 projectors and a block of >= 128 bands)].  out has room for n
- * values (up to 12).
- * The plane path is chosen by LDS fit and box shape: the lane-pair kernel
- * serves the mixed form when N1 = N2 is one of its compiled sizes (even,
- * 16..90), the lane-quad kernel the FP64 form when N1 = N2 is one of its
- * compiled sizes (multiples of 4, 16..72).  Environment variables read by qeh_ctx_plan / qeh_ctx_create:
+ * precision, plane path (0 one kernel, 1 split through HBM; 2 and 4: one
+ * kernel, on a box whose density runs the lane-pair / lane-quad passes),
+ * stick path (0 LDS passes, 1 lane-pair register z transforms), projector
+ * tiles (0 the 64-row MFMA tiles, 1 the wide single-precision tiles:
+ * QEH_MIXED with >= 2048 projectors and a block of >= 128 bands)].  out has
+ * room for n values (up to 12).
+ * The plane pass takes the two-factor kernel on square planes (N1 = N2) of a
+ * compiled size (products of 2, 3, 5 and 7 up to 192 with two factors of at
+ * most 16, and 125) whose x-extent columns fit in LDS, else LDS passes of
+ * small radices.  Environment variables read by qeh_ctx_plan / qeh_ctx_create:
  * QEH_FORCE_SPLIT_PLANE=1 forces the split path (a test hook);
  * QEH_STICK_KERNEL=generic keeps the LDS-pass z transforms where the lane-pair
  * ones would run (mixed form, N3 a compiled size; a test hook);
- * QEH_PLANE_KERNEL=generic keeps the fused kernel where a register one
- * would run (a test and comparison hook); QEH_PAIR_PLANES=n sets the bands per
- * register-kernel workgroup (default 2 lane-pair, 1 lane-quad); QEH_PLANE_ROWS=n caps the rows the fused
- * plane kernel expands at once (a tuning knob; fewer rows use less LDS). */
+ * QEH_PLANE_KERNEL=generic keeps the LDS-pass plane kernel where the two-factor
+ * one would run (a test and comparison hook); QEH_PLANE_ROWS=n caps the rows
+ * the LDS-pass plane kernel expands at once (a tuning knob; fewer rows use
+ * less LDS). */
 qeh_status qeh_ctx_info(const qeh_ctx *ctx, long *out, int n);
 
 const char *qeh_status_str(qeh_status s);

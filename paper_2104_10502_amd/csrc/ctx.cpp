@@ -107,6 +107,7 @@ namespace {
 
 struct HostMaps {
   int nst = 0, hmin = 0, ext = 0;
+  int kmin = 0, kmax = 0;
   int npw_fft = 0;                  // G-vectors the FFT path places (the full sphere)
   std::vector<int> stick_off, stick_h, stick_k;
   std::vector<int> full;            // Gamma cells: the full sphere's Miller list
@@ -203,6 +204,8 @@ qeh_status validate(const qeh_cell *c, HostMaps *hm) {
   hm->nst = (int)hm->stick_h.size();
   hm->hmin = lo[0];
   hm->ext = hi[0] - lo[0] + 1;
+  hm->kmin = lo[1];
+  hm->kmax = hi[1];
   // finiteness of the numeric inputs
   const long nfft = (long)c->fft[0] * c->fft[1] * c->fft[2];
   for (long i = 0; i < nfft; ++i)
@@ -251,7 +254,7 @@ qeh_status validate(const qeh_cell *c, HostMaps *hm) {
 // Arena layout, shared by plan and create.
 struct Layout {
   size_t off_stick_off, off_gmap, off_tidx, off_tidx_dit, off_xin, off_kin, off_hdiag, off_vs,
-      off_tw, off_beta, off_dmat, off_qmat, off_pj0, off_pnb, off_pdoff, off_chunk, off_sbuf, off_part,
+      off_tidx2, off_tw, off_beta, off_dmat, off_qmat, off_pj0, off_pnb, off_pdoff, off_chunk, off_sbuf, off_part,
       off_ps, off_big, off_colstart, off_psi32, off_pgen, off_gbuf;
   size_t total;
 };
@@ -268,6 +271,7 @@ struct Geometry {
   PlaneGeom pg;
   SplitGeom spg;
   StickGeom sg;
+  TwoGeom two;
 };
 
 void geometry(const qeh_cell *c, const HostMaps &hm, Geometry *g) {
@@ -336,23 +340,20 @@ void geometry(const qeh_cell *c, const HostMaps &hm, Geometry *g) {
       g->pg.lds_bytes = plane_lds_bytes(prec, hm.ext, n1, n2, g->pg);
     }
   }
-  // lane-pair kernel (N1 = N2 with a compiled form, single precision): pb bands
-  // of one plane per workgroup, 2 by default (QEH_PAIR_PLANES=n overrides);
-  // QEH_PLANE_KERNEL=generic keeps the fused kernel (comparison and test hook)
-  g->pg.pb = 0;
-  g->pg.lds_pair = 0;
-  if (g->plane_path == 0 && pair_plane_supported(prec, n1, n2)) {
+  // two-factor kernel (square planes of a compiled size whose columns fit in
+  // LDS): faster than the LDS-pass and the split kernels at every size measured
+  // (1.5 to 4.2 times, 12 .. 180).  Plane paths 2 and 4 name the sizes whose
+  // density passes take natural-order y tables.  QEH_PLANE_KERNEL=generic and
+  // QEH_FORCE_SPLIT_PLANE=1 keep the LDS-pass kernels (test hooks).
+  g->two = TwoGeom{};
+  {
     const char *kern = std::getenv("QEH_PLANE_KERNEL");
-    const bool generic = kern && std::strcmp(kern, "generic") == 0;
-    const char *pbs = std::getenv("QEH_PAIR_PLANES");
-    int pb = pbs ? std::atoi(pbs) : 2;
-    pb = std::max(1, std::min(8, pb));
-    while (pb > 1 && pair_plane_lds_bytes(prec, hm.ext, n2, pb) > (size_t)kLdsMax) --pb;
-    if (!generic && pair_plane_lds_bytes(prec, hm.ext, n2, pb) <= (size_t)kLdsMax) {
-      g->plane_path = 2;
-      g->pg.pb = pb;
-      g->pg.lds_pair = pair_plane_lds_bytes(prec, hm.ext, n2, pb);
-    }
+    const char *force = std::getenv("QEH_FORCE_SPLIT_PLANE");
+    const bool keep = (kern && std::strcmp(kern, "generic") == 0) || (force && force[0] == '1');
+    if (!keep && two_geometry(prec, n1, n2, hm.ext, hm.kmax - hm.kmin + 1, &g->two))
+      g->plane_path = pair_plane_supported(prec, n1, n2)   ? 2
+                      : quad_plane_supported(prec, n1, n2) ? 4
+                                                           : 0;
   }
   // lane-pair K1 / K3 (single precision, N3 with a compiled form);
   // QEH_STICK_KERNEL=generic keeps the LDS-pass kernels (test hook)
@@ -360,23 +361,6 @@ void geometry(const qeh_cell *c, const HostMaps &hm, Geometry *g) {
   if (pair_z_supported(prec, n3) && pair_z_lds_bytes(n3) <= (size_t)kLdsMax) {
     const char *kern = std::getenv("QEH_STICK_KERNEL");
     if (!(kern && std::strcmp(kern, "generic") == 0)) g->zpair = 1;
-  }
-  // lane-quad kernel (N1 = N2 a compiled size: FP64 up to 72, single
-  // precision above the lane-pair sizes): one band per workgroup by default
-  // (QEH_PAIR_PLANES overrides); QEH_PLANE_KERNEL=generic keeps the fused
-  // kernel
-  if (g->plane_path == 0 && quad_plane_supported(prec, n1, n2)) {
-    const char *kern = std::getenv("QEH_PLANE_KERNEL");
-    const bool generic = kern && std::strcmp(kern, "generic") == 0;
-    const char *pbs = std::getenv("QEH_PAIR_PLANES");
-    int pb = pbs ? std::atoi(pbs) : 1;
-    pb = std::max(1, std::min(8, pb));
-    while (pb > 1 && quad_plane_lds_bytes(prec, hm.ext, n2, pb) > (size_t)kLdsMax) --pb;
-    if (!generic && quad_plane_lds_bytes(prec, hm.ext, n2, pb) <= (size_t)kLdsMax) {
-      g->plane_path = 4;
-      g->pg.pb = pb;
-      g->pg.lds_pair = quad_plane_lds_bytes(prec, hm.ext, n2, pb);
-    }
   }
   g->pg.ext_div = make_fastdiv(hm.ext);
   g->pg.rc_div = make_fastdiv(g->pg.rc);
@@ -436,6 +420,7 @@ Layout layout(const qeh_cell *c, const HostMaps &hm, const Geometry &g) {
   L.off_gmap = bump(&cur, 4 * (size_t)hm.npw_fft);
   L.off_tidx = bump(&cur, 4 * (size_t)hm.nst);
   L.off_tidx_dit = bump(&cur, 4 * (size_t)hm.nst);
+  L.off_tidx2 = bump(&cur, g.two.on ? 4 * (size_t)hm.nst : 0);
   L.off_xin = bump(&cur, 4 * (size_t)c->fft[0]);
   L.off_kin = bump(&cur, 8 * (size_t)c->npw);
   L.off_hdiag = bump(&cur, 8 * (size_t)c->npw);
@@ -566,6 +551,7 @@ qeh_status qeh_ctx_create(const qeh_cell *cell, void *arena, size_t arena_bytes,
   c->pg = g.pg;
   c->spg = g.spg;
   c->sg = g.sg;
+  c->two = g.two;
   c->stream = reinterpret_cast<hipStream_t>(hip_stream);
   c->arena = reinterpret_cast<char *>(arena);
   c->arena_bytes = arena_bytes;
@@ -574,6 +560,7 @@ qeh_status qeh_ctx_create(const qeh_cell *cell, void *arena, size_t arena_bytes,
   c->d.gmap = reinterpret_cast<int *>(A + L.off_gmap);
   c->d.tidx = reinterpret_cast<int *>(A + L.off_tidx);
   c->d.tidx_dit = reinterpret_cast<int *>(A + L.off_tidx_dit);
+  c->d.tidx2 = g.two.on ? reinterpret_cast<int *>(A + L.off_tidx2) : nullptr;
   c->d.xin = reinterpret_cast<int *>(A + L.off_xin);
   c->d.kin = reinterpret_cast<double *>(A + L.off_kin);
   c->d.hdiag = reinterpret_cast<double *>(A + L.off_hdiag);
@@ -599,7 +586,7 @@ qeh_status qeh_ctx_create(const qeh_cell *cell, void *arena, size_t arena_bytes,
   const size_t nfft = (size_t)n1 * n2 * n3;
   const bool f64 = c->prec == QEH_FP64;
   // ---- host-side maps
-  std::vector<int> gmap(hm.npw_fft), tidx(hm.nst), tidx_dit(hm.nst), xin(n1, -1);
+  std::vector<int> gmap(hm.npw_fft), tidx(hm.nst), tidx_dit(hm.nst), tidx2, xin(n1, -1);
   const int *mf = hm.miller_fft;
   for (int s = 0; s < hm.nst; ++s) {
     for (int gg = hm.stick_off[s]; gg < hm.stick_off[s + 1]; ++gg)
@@ -609,6 +596,13 @@ qeh_status qeh_ctx_create(const qeh_cell *cell, void *arena, size_t arena_bytes,
     tidx_dit[s] = (hm.stick_h[s] - hm.hmin) * c->pg.ldT + fft_digit_pos(c->dy, ky);
     tidx[s] = (c->plane_path == 2 || c->plane_path == 4) ? (hm.stick_h[s] - hm.hmin) * c->pg.ldT + ky
                                                           : tidx_dit[s];
+  }
+  if (c->two.on) {
+    tidx2.resize(hm.nst);
+    for (int s = 0; s < hm.nst; ++s) {
+      const int p = hm.stick_k[s] - hm.kmin;
+      tidx2[s] = (hm.stick_h[s] - hm.hmin) * c->two.ldT + p / c->two.b * c->two.bp + p % c->two.b;
+    }
   }
   for (int cc = 0; cc < hm.ext; ++cc) xin[fft_digit_pos(c->dx, imod(hm.hmin + cc, n1))] = cc;
   std::vector<int> colstart(hm.ext + 1, hm.nst);
@@ -698,6 +692,7 @@ qeh_status qeh_ctx_create(const qeh_cell *cell, void *arena, size_t arena_bytes,
   up(c->d.gmap, gmap.data(), 4 * gmap.size());
   up(c->d.tidx, tidx.data(), 4 * tidx.size());
   up(c->d.tidx_dit, tidx_dit.data(), 4 * tidx_dit.size());
+  if (c->two.on) up(c->d.tidx2, tidx2.data(), 4 * tidx2.size());
   up(c->d.xin, xin.data(), 4 * xin.size());
   up(c->d.colstart, colstart.data(), 4 * colstart.size());
   up(c->d.kin, kin.data(), 8 * kin.size());

@@ -452,120 +452,8 @@ __global__ __launch_bounds__(kPT) void k2_plane(
   for (int s = tid; s < nst; s += kPT) plane[s] = T[tidx[s]];
 }
 
-// ---------------------------------------------------------------- K2, lane pairs
-// Plane pass with every line transform held in registers, for boxes with
-// N1 = N2 = N even and a compiled form of N.  Each line (a y column of the
-// x-extent tile, or a full x row) belongs to two adjacent lanes that hold one
-// half of it each (pair_inv / pair_fwd), so a transform costs one LDS load and
-// one LDS store per point, with compile-time indices and twiddles.
-// Rows: the x-extent column c = h - hmin sits at x position c instead of
-// h mod N.  The shift multiplies the inverse row transform by
-// exp(2 pi i hmin x / N) and the forward transform by its conjugate; V(r) is
-// real, so the two phases cancel and the values returned on the columns are
-// those of the unshifted transform.  Row positions c >= ext load from a zero
-// slot and store to a per-thread discard slot, which keeps every lane on one
-// path.  Column y positions are natural (tidx holds c*LD + (k mod N)).
-// One workgroup: pb bands of one z plane (they read the same V rows), with the
-// XCD-aware id remap of the fused kernel.
+// ---------------------------------------------------------------- density threads
 constexpr int kRT = 256;
-
-// Register budget: three waves per SIMD (<= 168 VGPRs) keeps three 2-band
-// workgroups resident per CU at N = 72 without spills, measured faster there
-// than two waves per SIMD; N = 90 needs the two-wave budget to avoid spills.
-template <typename C, int N>
-__global__ __launch_bounds__(kRT) __attribute__((amdgpu_waves_per_eu(N < 90 ? 3 : 2))) void k2_plane_pair(
-    C *__restrict__ sbuf, const typename real_of<C>::type *__restrict__ vs,
-    const int *__restrict__ tidx, int nst, int n3, int ext, int pb, int nbk, int ngrp,
-    int per_xcd) {
-  using R = typename real_of<C>::type;
-  constexpr int LD = N | 1, M = N / 2;
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  C *T = reinterpret_cast<C *>(smem_raw);
-  const int id = blockIdx.x;
-  const int logical = (id & 7) * per_xcd + (id >> 3);
-  if (logical >= ngrp * n3) return;
-  const int z = logical / ngrp;
-  const int g = logical - z * ngrp;
-  const int b0 = g * pb;
-  const int np = min(pb, nbk - b0);
-  const int tid = threadIdx.x;
-  const int tile = ext * LD;
-  const C *zslot = T + pb * tile;
-  C *dslot = T + pb * tile + 1 + tid;
-  const C zero = cmk<C>(0, 0);
-
-  for (int i = tid; i < np * tile; i += kRT) T[i] = zero;
-  if (tid == 0) T[pb * tile] = zero;
-  __syncthreads();
-  for (int p = 0; p < np; ++p) {
-    const C *plane = sbuf + ((size_t)(b0 + p) * n3 + z) * nst;
-    C *Tp = T + p * tile;
-    for (int s = tid; s < nst; s += kRT) Tp[tidx[s]] = plane[s];
-  }
-  __syncthreads();
-
-  // inverse y transforms of the np * ext columns
-  for (int j = tid; j < 2 * np * ext; j += kRT) {
-    const bool odd = j & 1;
-    C *col = T + (j >> 1) * LD;
-    C v[M];
-#pragma unroll
-    for (int n = 0; n < M; ++n) v[n] = col[2 * n + odd];
-    regfft::pair_inv<C, N>(v, odd);
-    C *out = col + (odd ? M : 0);
-#pragma unroll
-    for (int k = 0; k < M; ++k) out[k] = v[k];
-  }
-  __syncthreads();
-
-  // rows: x inverse, V(r)/N, x forward
-  for (int j = tid; j < 2 * np * N; j += kRT) {
-    const bool odd = j & 1;
-    const int r = j >> 1;
-    const int p = r / N;
-    const int y = r - p * N;
-    C *row = T + p * tile + y;
-    const int l = odd ? 1 : 0;
-    C v[M];
-#pragma unroll
-    for (int n = 0; n < M; ++n) {
-      const int c = 2 * n + l;
-      const C *a = c < ext ? row + c * LD : zslot;
-      v[n] = *a;
-    }
-    regfft::pair_inv<C, N>(v, odd);
-    const R *vr = vs + ((size_t)z * N + y) * N + l * M;
-#pragma unroll
-    for (int x = 0; x < M; ++x) v[x] = cscale(v[x], vr[x]);
-    regfft::pair_fwd<C, N>(v, odd);
-#pragma unroll
-    for (int m = 0; m < M; ++m) {
-      const int c = 2 * m + l;
-      C *a = c < ext ? row + c * LD : dslot;
-      *a = v[m];
-    }
-  }
-  __syncthreads();
-
-  // forward y transforms
-  for (int j = tid; j < 2 * np * ext; j += kRT) {
-    const bool odd = j & 1;
-    C *col = T + (j >> 1) * LD;
-    const C *in = col + (odd ? M : 0);
-    C v[M];
-#pragma unroll
-    for (int x = 0; x < M; ++x) v[x] = in[x];
-    regfft::pair_fwd<C, N>(v, odd);
-#pragma unroll
-    for (int m = 0; m < M; ++m) col[2 * m + odd] = v[m];
-  }
-  __syncthreads();
-  for (int p = 0; p < np; ++p) {
-    C *plane = sbuf + ((size_t)(b0 + p) * n3 + z) * nst;
-    const C *Tp = T + p * tile;
-    for (int s = tid; s < nst; s += kRT) plane[s] = Tp[tidx[s]];
-  }
-}
 
 // ---------------------------------------------------------------- density
 // Charge density generation: rho(r) = (1/Omega) sum_b occ_b |psi_b(r)|^2.
@@ -854,143 +742,16 @@ __global__ __launch_bounds__(256) void density_reduce(const double *__restrict__
   }
 }
 
-// ---------------------------------------------------------------- K2, lane quads / octets
-// Register plane pass for N1 = N2 = N with a compiled form: each line belongs
-// to L adjacent lanes holding N/L points each (L = 4: quad_inv / quad_fwd;
-// L = 8, single precision: oct_inv / oct_fwd).  The inverse returns
-// lane-bit-reversed blocks, which is the forward's input layout, so the row
-// chain inverse -> V -> forward moves no data.  The x-extent shift of the rows
-// and the zero / discard slots are those of the lane-pair kernel.  One band per
-// workgroup by default.  FP64 (lane quads, N <= 72, 256 threads): the column
-// tile is 42 KB at N = 72.  Single precision (the boxes above the lane-pair
-// sizes, 512 threads): lane quads at N = 96, lane octets at N >= 120 (20 points
-// per lane at N = 160, where quads need 40 and spill); at the 512-atom cell
-// one workgroup (89 KB of column tile for its x-extent of 69) fills a CU.
-template <int L> __device__ __forceinline__ int lane_rev(int o) {
-  return L == 4 ? (((o & 1) << 1) | (o >> 1)) : (((o & 1) << 2) | (o & 2) | (o >> 2));
-}
-
-template <typename C, int N, int L> struct LineLanes;
-template <typename C, int N> struct LineLanes<C, N, 4> {
-  regfft::QuadLane<typename real_of<C>::type> ql;
-  __device__ explicit LineLanes(int o) : ql(o) {}
-  __device__ void inv(C *v, const C *tw) const { regfft::quad_inv<C, N>(v, tw, ql); }
-  __device__ void fwd(C *v, const C *tw) const { regfft::quad_fwd<C, N>(v, tw, ql); }
-};
-template <int N> struct LineLanes<float2, N, 8> {
-  regfft::OctLane ol;
-  __device__ explicit LineLanes(int o) : ol(o) {}
-  __device__ void inv(float2 *v, const float2 *tw) const { regfft::oct_inv<N>(v, tw, ol); }
-  __device__ void fwd(float2 *v, const float2 *tw) const { regfft::oct_fwd<N>(v, tw, ol); }
-};
-
-template <typename C, int N, int NT, int L>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(
-    NT > 256 ? 2 : (N < 48 ? 3 : 2)))) void k2_plane_lanes(
-    C *__restrict__ sbuf, const typename real_of<C>::type *__restrict__ vs,
-    const int *__restrict__ tidx, const C *__restrict__ tw_g, int nst, int n3, int ext, int pb,
-    int nbk, int ngrp, int per_xcd) {
-  using R = typename real_of<C>::type;
-  constexpr int LD = N | 1, Q = N / L;
-  static_assert(Q * L == N, "N must be a multiple of the lanes per line");
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  C *T = reinterpret_cast<C *>(smem_raw);
-  const int id = blockIdx.x;
-  const int logical = (id & 7) * per_xcd + (id >> 3);
-  if (logical >= ngrp * n3) return;
-  const int z = logical / ngrp;
-  const int g = logical - z * ngrp;
-  const int b0 = g * pb;
-  const int np = min(pb, nbk - b0);
-  const int tid = threadIdx.x;
-  const int tile = ext * LD;
-  const C *zslot = T + pb * tile;
-  C *dslot = T + pb * tile + 1 + tid;
-  C *twl = T + pb * tile + 1 + NT;   // [L][Q]: row o holds W_N^{o k}
-  const C zero = cmk<C>(0, 0);
-  const int o = tid & (L - 1);
-  const int bo = lane_rev<L>(o);
-  const LineLanes<C, N, L> ln(o);
-  const C *tw = twl + o * Q;
-
-  for (int i = tid; i < np * tile; i += NT) T[i] = zero;
-  if (tid == 0) T[pb * tile] = zero;
-  for (int i = tid; i < L * Q; i += NT) twl[i] = tw_g[((i / Q) * (i % Q)) % N];
-  __syncthreads();
-  for (int p = 0; p < np; ++p) {
-    const C *plane = sbuf + ((size_t)(b0 + p) * n3 + z) * nst;
-    C *Tp = T + p * tile;
-    for (int s = tid; s < nst; s += NT) Tp[tidx[s]] = plane[s];
-  }
-  __syncthreads();
-  for (int j = tid; j < L * np * ext; j += NT) {
-    C *col = T + (j / L) * LD;
-    C v[Q];
-#pragma unroll
-    for (int n = 0; n < Q; ++n) v[n] = col[L * n + o];
-    ln.inv(v, tw);
-    C *out = col + Q * bo;
-#pragma unroll
-    for (int k = 0; k < Q; ++k) out[k] = v[k];
-  }
-  __syncthreads();
-  for (int j = tid; j < L * np * N; j += NT) {
-    const int r = j / L;
-    const int p = r / N;
-    const int y = r - p * N;
-    C *row = T + p * tile + y;
-    C v[Q];
-#pragma unroll
-    for (int n = 0; n < Q; ++n) {
-      const int c = L * n + o;
-      const C *a = c < ext ? row + c * LD : zslot;
-      v[n] = *a;
-    }
-    ln.inv(v, tw);
-    const R *vr = vs + ((size_t)z * N + y) * N + Q * bo;
-#pragma unroll
-    for (int k = 0; k < Q; ++k) v[k] = cscale(v[k], vr[k]);
-    ln.fwd(v, tw);
-#pragma unroll
-    for (int m = 0; m < Q; ++m) {
-      const int c = L * m + o;
-      C *a = c < ext ? row + c * LD : dslot;
-      *a = v[m];
-    }
-  }
-  __syncthreads();
-  for (int j = tid; j < L * np * ext; j += NT) {
-    C *col = T + (j / L) * LD;
-    const C *in = col + Q * bo;
-    C v[Q];
-#pragma unroll
-    for (int x = 0; x < Q; ++x) v[x] = in[x];
-    ln.fwd(v, tw);
-#pragma unroll
-    for (int m = 0; m < Q; ++m) col[L * m + o] = v[m];
-  }
-  __syncthreads();
-  for (int p = 0; p < np; ++p) {
-    C *plane = sbuf + ((size_t)(b0 + p) * n3 + z) * nst;
-    const C *Tp = T + p * tile;
-    for (int s = tid; s < nst; s += NT) plane[s] = Tp[tidx[s]];
-  }
-}
-
-// threads of the lane-quad / lane-octet plane workgroup: 256 in FP64, 512 in
-// single precision (two waves per SIMD)
-constexpr int quad_plane_threads(bool fp64, int n) { return fp64 ? kRT : 512; }
-// lanes per line: octets for the single-precision boxes of >= 120 points
-constexpr int plane_lanes(bool fp64, int n) { return !fp64 && n >= 120 ? 8 : 4; }
-
-// Box sizes with a compiled lane-quad kernel (double precision).
+// ---------------------------------------------------------------- compiled sizes
+// Square boxes of these sizes report plane path 4 (double precision); the lane-quad
+// density pass is compiled for them.
 #define QEH_QUAD_SIZES(X) X(16) X(20) X(24) X(32) X(36) X(40) X(48) X(60) X(64) X(72)
 
-// Box sizes with a compiled single-precision lane-quad kernel (above the
-// lane-pair sizes).
+// ... and in single precision (no density pass of their own).
 #define QEH_QUAD32_SIZES(X) X(96) X(120) X(128) X(144) X(160)
 
-// Box sizes with a compiled lane-pair kernel (single precision).
+// Sizes of the lane-pair z transforms (single precision); square boxes of these
+// sizes report plane path 2.
 #define QEH_PAIR_SIZES(X) \
   X(16) X(18) X(20) X(24) X(30) X(32) X(36) X(40) X(48) X(50) X(54) X(60) X(64) X(72) X(80) X(90)
 // ... and for the density kernels, whose per-point sums add registers (N = 90
@@ -1268,28 +1029,6 @@ template <typename C> hipError_t k2_impl(const qeh_ctx *c, int nbk) {
   return hipGetLastError();
 }
 
-template <int N> hipError_t k2_pair_launch(const qeh_ctx *c, int nbk) {
-  const int pb = c->pg.pb;
-  const int ngrp = (nbk + pb - 1) / pb;
-  const int per_xcd = (ngrp * c->n3 + 7) / 8;
-  allow_lds(k2_plane_pair<float2, N>, c->pg.lds_pair);
-  hipLaunchKernelGGL((k2_plane_pair<float2, N>), dim3(8 * per_xcd), dim3(kRT), c->pg.lds_pair,
-                     c->stream, reinterpret_cast<float2 *>(c->d.sbuf),
-                     reinterpret_cast<const float *>(c->d.vs), c->d.tidx, c->nst, c->n3, c->ext,
-                     pb, nbk, ngrp, per_xcd);
-  return hipGetLastError();
-}
-
-hipError_t k2_pair_impl(const qeh_ctx *c, int nbk) {
-  switch (c->n1) {
-#define QEH_PAIR_CASE(NN) \
-  case NN: return k2_pair_launch<NN>(c, nbk);
-    QEH_PAIR_SIZES(QEH_PAIR_CASE)
-#undef QEH_PAIR_CASE
-    default: return hipErrorInvalidValue;
-  }
-}
-
 template <typename C> hipError_t density_columns_impl(const qeh_ctx *c, int nbk, void *big_v) {
   const C *tw = reinterpret_cast<const C *>(c->d.tw);
   const SplitGeom &g = c->spg;
@@ -1408,41 +1147,6 @@ hipError_t k3_pair_impl(const qeh_ctx *c, int nbk, const double2 *psi, int ldpsi
   }
 }
 
-template <typename C, int N> hipError_t k2_quad_launch(const qeh_ctx *c, int nbk) {
-  using R = typename real_of<C>::type;
-  constexpr int NT = quad_plane_threads(sizeof(R) == 8, N);
-  constexpr int L = plane_lanes(sizeof(R) == 8, N);
-  const int pb = c->pg.pb;
-  const int ngrp = (nbk + pb - 1) / pb;
-  const int per_xcd = (ngrp * c->n3 + 7) / 8;
-  allow_lds(k2_plane_lanes<C, N, NT, L>, c->pg.lds_pair);
-  hipLaunchKernelGGL((k2_plane_lanes<C, N, NT, L>), dim3(8 * per_xcd), dim3(NT), c->pg.lds_pair,
-                     c->stream, reinterpret_cast<C *>(c->d.sbuf),
-                     reinterpret_cast<const R *>(c->d.vs), c->d.tidx,
-                     reinterpret_cast<const C *>(c->d.tw) + c->tw_off[0], c->nst, c->n3, c->ext,
-                     pb, nbk, ngrp, per_xcd);
-  return hipGetLastError();
-}
-
-hipError_t k2_quad_impl(const qeh_ctx *c, int nbk) {
-  if (c->prec == QEH_FP64) {
-    switch (c->n1) {
-#define QEH_QUAD_CASE(NN) \
-  case NN: return k2_quad_launch<double2, NN>(c, nbk);
-      QEH_QUAD_SIZES(QEH_QUAD_CASE)
-#undef QEH_QUAD_CASE
-      default: return hipErrorInvalidValue;
-    }
-  }
-  switch (c->n1) {
-#define QEH_QUAD_CASE(NN) \
-  case NN: return k2_quad_launch<float2, NN>(c, nbk);
-    QEH_QUAD32_SIZES(QEH_QUAD_CASE)
-#undef QEH_QUAD_CASE
-    default: return hipErrorInvalidValue;
-  }
-}
-
 }  // namespace
 
 size_t plane_lds_bytes(int prec, int ext, int n1, int n2, const PlaneGeom &g) {
@@ -1545,13 +1249,6 @@ bool quad_plane_supported(int prec, int n1, int n2) {
   }
 }
 
-size_t quad_plane_lds_bytes(int prec, int ext, int n2, int pb) {
-  const bool f64 = prec == QEH_FP64;
-  const size_t c = f64 ? 16 : 8;
-  // column tiles, zero slot, discard slots, the [4][N/4] twiddle table
-  return c * ((size_t)pb * ext * (n2 | 1) + 1 + quad_plane_threads(f64, n2) + n2);
-}
-
 size_t pair_z_lds_bytes(int n3) { return 8 * (size_t)kPairSticks * (n3 | 1); }
 
 bool pair_plane_supported(int prec, int n1, int n2) {
@@ -1563,12 +1260,6 @@ bool pair_plane_supported(int prec, int n1, int n2) {
 #undef QEH_PAIR_CASE
     default: return false;
   }
-}
-
-size_t pair_plane_lds_bytes(int prec, int ext, int n2, int pb) {
-  const size_t c = prec == QEH_FP64 ? 16 : 8;
-  // column tiles, zero slot, discard slots
-  return c * ((size_t)pb * ext * (n2 | 1) + 1 + kRT);
 }
 
 size_t stick_lds_bytes(int prec, int n3, const StickGeom &g) {
@@ -1597,8 +1288,8 @@ hipError_t launch_k1_gamma(const qeh_ctx *c, int nbk, const double2 *psi, int ld
 }
 
 hipError_t launch_k2(const qeh_ctx *c, int nbk) {
-  if (c->plane_path == 2) return k2_pair_impl(c, nbk);
-  if (c->plane_path == 4) return k2_quad_impl(c, nbk);
+  if (c->two.on)
+    return c->prec == QEH_FP64 ? launch_k2_two_f64(c, nbk) : launch_k2_two_f32(c, nbk);
   if (c->plane_path != 0)
     return c->prec == QEH_FP64 ? k2_split_impl<double2>(c, nbk) : k2_split_impl<float2>(c, nbk);
   return c->prec == QEH_FP64 ? k2_impl<double2>(c, nbk) : k2_impl<float2>(c, nbk);

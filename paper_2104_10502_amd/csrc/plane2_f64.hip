@@ -1,0 +1,16 @@
+// Two-factor plane pass, double precision (see plane2.h).
+#include "plane2.h"
+
+namespace qeh {
+
+hipError_t launch_k2_two_f64(const qeh_ctx *c, int nbk) {
+  switch (c->n1) {
+#define QEH_TWO_CASE(NN) \
+  case NN: return plane2::launch<double2, NN>(c, nbk);
+    QEH_TWO_SIZES(QEH_TWO_CASE)
+#undef QEH_TWO_CASE
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace qeh

@@ -48,8 +48,6 @@ struct PlaneGeom {
   int ldR;   // row stride of the row buffer (>= N1, odd)
   size_t lds_bytes;
   FastDiv ext_div, rc_div, rlast_div;   // ext, rc, rows of the last chunk
-  int pb;            // lane-pair kernel: planes (bands of one z) per workgroup
-  size_t lds_pair;   // lane-pair kernel: LDS bytes per workgroup
 };
 
 // Split plane path (planes too large for LDS): column groups of cg columns,
@@ -58,6 +56,13 @@ struct SplitGeom {
   int cg, rg, ldl;
   size_t lds_col, lds_row;
   FastDiv cg_div, cglast_div, rg_div, rglast_div;
+};
+
+// Two-factor plane kernel (plane2.h): whether it runs, its column pitch, the
+// split of a y position p into slot (p / b) * bp + p % b, rows at a time.
+struct TwoGeom {
+  int on, half, rc, ldT, b, bp;
+  size_t lds;
 };
 
 struct StickGeom {
@@ -73,7 +78,8 @@ struct DevMaps {
   int *gmap;         // [npw] s*ldz + digit-reversed z position (natural z for the
                      // lane-pair K1 / K3, whose ldz is N3 | 1 as well)
   int *tidx;         // [nst] plane-tile index c*ldT + pos_y(k mod N2); the lane-pair
-                     // and lane-quad kernels take natural y (pos_y = identity)
+                     // and lane-quad density passes take natural y (pos_y = identity)
+  int *tidx2;        // [nst] the same for the two-factor plane kernel (y shifted to k - kmin)
   int *tidx_dit;     // [nst] the same with pos_y the y-DIT input position (always)
   int *xin;          // [N1] column c whose h sits at x-DIT input position p, or -1
   double *kin;       // [npw] |k+G|^2
@@ -106,8 +112,8 @@ struct qeh_ctx {
   int has_q = 0;        // 1: overlap q blocks present (S != 1)
   int n1 = 0, n2 = 0, n3 = 0, ext = 0, hmin = 0;
   int block = 0, prec = 0;
-  int plane_path = 0;   // 0 fused plane kernel, 1 split through HBM, 2 lane-pair kernel,
-                        // 4 lane-quad kernel (FP64)
+  int plane_path = 0;   // 0 one kernel, 1 split through HBM; 2, 4: one kernel, natural-order
+                        // y tables for the lane-pair / lane-quad density passes
   int zpair = 0;        // 1: lane-pair K1 / K3 (gmap at natural z)
   int nsplit = 1, kchunk = 0;
   int wide = 0;         // 1: wide single-precision tiles for the projector products
@@ -118,6 +124,7 @@ struct qeh_ctx {
   qeh::PlaneGeom pg{};
   qeh::SplitGeom spg{};
   qeh::StickGeom sg{};
+  qeh::TwoGeom two{};
   int tw_off[3] = {0, 0, 0};
   hipStream_t stream = nullptr;
   qeh::DevMaps d{};
@@ -153,14 +160,18 @@ hipError_t launch_k3(const qeh_ctx *c, int nbk, const double2 *psi, int ldpsi,
                      double2 *hpsi, int ldh, int add_kinetic);
 size_t plane_lds_bytes(int prec, int ext, int n1, int n2, const PlaneGeom &g);
 size_t stick_lds_bytes(int prec, int n3, const StickGeom &g);
-// Lane-pair plane kernel: whether a compiled form exists for this precision and
-// box, and its LDS bytes for pb planes of ext columns.
+// Square boxes whose density passes are the lane-pair (single precision) or
+// lane-quad (FP64) kernels; lane-pair z transforms for N3.
 bool pair_plane_supported(int prec, int n1, int n2);
 bool pair_z_supported(int prec, int n3);
 bool quad_plane_supported(int prec, int n1, int n2);
 size_t pair_z_lds_bytes(int n3);
-size_t pair_plane_lds_bytes(int prec, int ext, int n2, int pb);
-size_t quad_plane_lds_bytes(int prec, int ext, int n2, int pb);
+
+// Two-factor plane kernel: geometry for an x-extent of ext columns and a y
+// extent of exty (false: no compiled form, or the columns exceed LDS).
+bool two_geometry(int prec, int n1, int n2, int ext, int exty, TwoGeom *g);
+hipError_t launch_k2_two_f32(const qeh_ctx *c, int nbk);
+hipError_t launch_k2_two_f64(const qeh_ctx *c, int nbk);
 
 // Charge density: row groups of rg rows, subgroups of bsub bands.
 struct DensityGeom {
