@@ -167,8 +167,10 @@ class CgRun {
 qeh_status CgRun::block_rr() {
   double2 *X = at<double2>(L_.X), *HX = at<double2>(L_.HX);
   ev_s_.start(s_);
-  ok(reduce_cols(c_, X, nb_, HX, nb_, at<double2>(L_.Hr), nb_, at<double2>(L_.part)));
-  ok(reduce_cols(c_, X, nb_, X, nb_, at<double2>(L_.Sr), nb_, at<double2>(L_.part)));
+  ok(reduce_cols(c_, X, nb_, HX, nb_, at<double2>(L_.Hr), nb_, at<double2>(L_.part),
+                    (size_t)kReduceMaxSplit * nb_ * nb_));
+  ok(reduce_cols(c_, X, nb_, X, nb_, at<double2>(L_.Sr), nb_, at<double2>(L_.part),
+                    (size_t)kReduceMaxSplit * nb_ * nb_));
   if (err_ != hipSuccess) return hip_fail(err_, "CG Rayleigh-Ritz products");
   qeh_status st = qeh_subspace_eigh(nb_, nb_, at<double>(L_.Hr), at<double>(L_.Sr), nb_,
                                     at<double>(L_.eig), at<double>(L_.Y), nb_, w_ + L_.eigw,
@@ -223,7 +225,8 @@ qeh_status CgRun::run(double2 *psi, int ldpsi, double *eig, double thr, int maxi
   for (int m = 0; m < nb; ++m) {
     double2 *x = X + (size_t)m * npw, *hx = HX + (size_t)m * npw;
     if (m > 0) {
-      ok(reduce_cols(c_, X, m, x, 1, coef, nb, at<double2>(L_.part)));
+      ok(reduce_cols(c_, X, m, x, 1, coef, nb, at<double2>(L_.part),
+                    (size_t)kReduceMaxSplit * nb_ * nb_));
       ok(launch_cg_project(x, X, npw, coef, m, npw, s_));
     }
     dots({{{x, x}, kCgXX}});
@@ -252,7 +255,8 @@ qeh_status CgRun::run(double2 *psi, int ldpsi, double *eig, double thr, int maxi
         break;
       }
       ++it;
-      ok(reduce_cols(c_, X, m + 1, g, 1, coef, nb, at<double2>(L_.part)));
+      ok(reduce_cols(c_, X, m + 1, g, 1, coef, nb, at<double2>(L_.part),
+                    (size_t)kReduceMaxSplit * nb_ * nb_));
       ok(launch_cg_project(g, X, npw, coef, m + 1, npw, s_));
       dots({{{g, r}, kCgGam}});
       ok(launch_cg_scalar(sc, 1, s_));

@@ -379,7 +379,10 @@ void geometry(const qeh_cell *c, const HostMaps &hm, Geometry *g) {
     }
   }
   // Projector products, split-K of beta^H psi in fixed chunks.
-  // FP64: 64 x 64 tiles, chunks of >= 256 plane waves, ~4 workgroups per CU.
+  // FP64: 64 x 64 tiles, chunks of >= 256 plane waves, ~4 workgroups per CU; flat
+  // tiles (cgemm_flat) three resident per CU, chunks of >= 64: the chunk's
+  // slices run one after the other, and at 16 bands x 8 projectors x 1 503 plane
+  // waves chunks of 304 took 42 us, of 64 take 5.
   // Single precision (split_gemm.hip): 64 x 64 tiles, 64 x 128 at Gamma (its
   // products do half the MFMA work per staged value), or 128 x 128 ("wide")
   // with >= 2048 projectors and blocks of >= 128 bands; workgroups for four
@@ -396,13 +399,15 @@ void geometry(const qeh_cell *c, const HostMaps &hm, Geometry *g) {
   g->ldb = f32 ? (c->npw + 15) / 16 * 16 : c->npw;
   g->wide = f32 && c->block >= 128 && g->nkb >= 2048 ? 1 : 0;
   if (g->nkb > 0) {
-    const int bm = g->wide ? 128 : 64;
+    const bool flat = !f32 && cgemm_flat(c->block, g->nkb, c->npw, 0);
+    const int bm = g->wide ? 128 : flat ? 16 : 64;
     const int bn = g->wide || (f32 && c->gamma) ? 128 : 64;
     const int tiles = ((c->block + bm - 1) / bm) * ((g->nkb + bn - 1) / bn);
     int ns = g->wide ? std::max(1, 4 * 256 / tiles)
              : f32   ? (2 * 256 + tiles - 1) / tiles
+             : flat  ? (3 * 256 + tiles - 1) / tiles
                      : std::max(1, (1024 + tiles - 1) / tiles);
-    ns = std::min(ns, std::max(1, c->npw / (f32 ? 64 : 256)));
+    ns = std::min(ns, std::max(1, c->npw / (f32 || flat ? 64 : 256)));
     int kc = (c->npw + ns - 1) / ns;
     kc = (kc + 15) / 16 * 16;
     g->kchunk = kc;

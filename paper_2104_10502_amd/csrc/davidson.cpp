@@ -96,13 +96,19 @@ qeh_status solver_bytes(int n, bool real, size_t *out) {
 // with ld.  K = npw is long: split into fixed chunks whose partial products
 // go to `part` and are summed in double in a fixed order.
 hipError_t reduce_cols(const qeh_ctx *c, const double2 *X, int nrow, const double2 *Y, int ncol,
-                       double2 *out, int ld, double2 *part) {
-  const int tiles = ((ncol + 63) / 64) * ((nrow + 63) / 64);
-  int ns = std::max(1, (512 + tiles - 1) / tiles);
-  ns = std::min(ns, std::max(1, c->npw / 256));
+                       double2 *out, int ld, double2 *part, size_t part_cap) {
+  // flat tiles (small products): short chunks, whose slices are the latency of
+  // the product (64 x 128, npw 1 791: 7 chunks of 256 took 42 us, 28 of 64 take 6)
+  const bool flat = cgemm_flat(ncol, nrow, c->npw, 0);
+  const int tiles = ((ncol + (flat ? 15 : 63)) / (flat ? 16 : 64)) * ((nrow + 63) / 64);
+  int ns = std::max(1, ((flat ? 768 : 512) + tiles - 1) / tiles);
+  ns = std::min(ns, std::max(1, c->npw / (flat ? 64 : 256)));
   ns = std::min(ns, kMaxSplit);
+  // the work area's partials are planned for ncol <= nb; a whole basis against
+  // itself (nrow = ncol = nbase) fits fewer
+  ns = (int)std::min<size_t>(ns, std::max<size_t>(1, part_cap / ((size_t)nrow * ncol)));
   int kc = (c->npw + ns - 1) / ns;
-  kc = (kc + 7) / 8 * 8;
+  kc = (kc + 15) / 16 * 16;
   ns = (c->npw + kc - 1) / kc;
   GemmDesc g{};
   g.A = Y;
@@ -375,6 +381,7 @@ qeh_status DavRun::init(qeh_ctx *c, int nb, double2 *psi, int ldpsi, double *eig
   Hw_ = reinterpret_cast<double2 *>(w + L_.Hw);
   Sw_ = reinterpret_cast<double2 *>(w + L_.Sw);
   part_ = reinterpret_cast<double2 *>(w + L_.part);
+  part_cap_ = (size_t)kMaxSplit * nb_ * nvecx_;
   X_ = reinterpret_cast<double2 *>(w + L_.X);
   Lc_ = reinterpret_cast<double2 *>(w + L_.Lc);
   LcH_ = reinterpret_cast<double2 *>(w + L_.LcH);
@@ -503,8 +510,8 @@ void DavRun::restart_from_ritz() {
     ok(launch_copy_rows(Q_, npw_, W_, npw_, npw_, nb_, s));
     if (gen_) ok(launch_copy_rows(SP_, npw_, U_, npw_, npw_, nb_, s));
   }
-  ok(reduce_cols(c_, V_, nb_, W_, nb_, Hr_, nvecx_, part_));
-  ok(reduce_cols(c_, V_, nb_, gen_ ? U_ : V_, nb_, Sr_, nvecx_, part_));
+  ok(reduce_cols(c_, V_, nb_, W_, nb_, Hr_, nvecx_, part_, part_cap_));
+  ok(reduce_cols(c_, V_, nb_, gen_ ? U_ : V_, nb_, Sr_, nvecx_, part_, part_cap_));
 }
 
 qeh_status DavRun::spsi(const double2 *x, double2 *y, int n) {
@@ -566,8 +573,8 @@ bool DavRun::advance() {
           phase_ = kDone;
           return true;
         }
-        ok(reduce_cols(c_, V_, nb, W_, nb, Hr_, nvecx, part_));
-        ok(reduce_cols(c_, V_, nb, gen_ ? U_ : V_, nb, Sr_, nvecx, part_));
+        ok(reduce_cols(c_, V_, nb, W_, nb, Hr_, nvecx, part_, part_cap_));
+        ok(reduce_cols(c_, V_, nb, gen_ ? U_ : V_, nb, Sr_, nvecx, part_, part_cap_));
         nbase_ = nb;
         phase_ = kRR;
         break;
@@ -760,8 +767,8 @@ bool DavRun::advance() {
             phase_ = kDone;
             return true;
           }
-          ok(reduce_cols(c_, V_, nbase_, W_, nbase_, Hr_, nvecx, part_));
-          if (gen_) ok(reduce_cols(c_, V_, nbase_, U_, nbase_, Sr_, nvecx, part_));
+          ok(reduce_cols(c_, V_, nbase_, W_, nbase_, Hr_, nvecx, part_, part_cap_));
+          if (gen_) ok(reduce_cols(c_, V_, nbase_, U_, nbase_, Sr_, nvecx, part_, part_cap_));
           phase_ = kRR;
           break;
         }
@@ -804,9 +811,9 @@ bool DavRun::advance() {
         }
         ev_s_.start(s);
         ok(reduce_cols(c_, V_, nbase_ + nc, W_ + (size_t)nbase_ * npw, nc,
-                       Hr_ + (size_t)nbase_ * nvecx, nvecx, part_));
+                       Hr_ + (size_t)nbase_ * nvecx, nvecx, part_, part_cap_));
         ok(reduce_cols(c_, V_, nbase_ + nc, (gen_ ? U_ : V_) + (size_t)nbase_ * npw, nc,
-                       Sr_ + (size_t)nbase_ * nvecx, nvecx, part_));
+                       Sr_ + (size_t)nbase_ * nvecx, nvecx, part_, part_cap_));
         ok(launch_herm_fill(Hr_, nvecx, nbase_, nbase_ + nc, s));
         ok(launch_herm_fill(Sr_, nvecx, nbase_, nbase_ + nc, s));
         ev_s_.stop(s);

@@ -92,6 +92,7 @@ class DavRun {
   DavLayout L_{};
   double2 *V_ = nullptr, *W_ = nullptr, *P_ = nullptr, *Q_ = nullptr;
   double2 *Hr_ = nullptr, *Sr_ = nullptr, *Hw_ = nullptr, *Sw_ = nullptr, *part_ = nullptr;
+  size_t part_cap_ = 0;   // split-K partials that fit in part_
   double2 *X_ = nullptr, *Lc_ = nullptr, *LcH_ = nullptr, *Y_ = nullptr;
   double *tri_ = nullptr, *Zt_ = nullptr, *escr_ = nullptr;   // own subspace solver
   bool own_ = false;

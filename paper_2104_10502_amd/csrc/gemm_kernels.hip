@@ -7,23 +7,25 @@
 // solver, which the paper runs through GPU BLAS (section "Evolution of the
 // GPU-enabled version").
 //
-// A complex product is three real MFMA products on planar (re, im) tiles
-// (Gauss's three-multiplication form):
+// A complex product of the large tiles is three real MFMA products (Gauss's
+// three-multiplication form, RM = 0):
 //   P1 += Ar Br,   P2 += Ai Bi,   P3 += (Ar + Ai)(Br + Bi),
 //   Cr = P1 - P2,  Ci = P3 - P1 - P2.
 // The operand sums are formed in registers after the LDS reads.  The form is
 // normwise stable; its rounding error is a small constant multiple of that of
 // the four-product form (Cr = Ar Br - Ai Bi, Ci = Ar Bi + Ai Br), and it issues
 // a quarter fewer MFMAs.  The kernels are held to three waves per SIMD (the
-// third accumulator set would otherwise push them to two).
+// third accumulator set would otherwise push them to two).  The flat tiles wait
+// for memory rather than for the MFMAs and take the four-product form (RM = 3).
 // Two cheaper forms serve the Gamma-point projections (RM = 1: only the real
-// part of C is wanted, Cr = P1 - P2; RM = 2: A is real, Cr = sum Ar Br and
-// Ci = sum Ar Bi): two MFMA products per step instead of three.
+// part of C is wanted; RM = 2: A is real, Cr = sum Ar Br and Ci = sum Ar Bi):
+// two MFMA products per step.
 // WGM x WGN waves (64 * WGM * WGN threads); each wave owns a
 // (BM/WGM) x (BN/WGN) block of C built from 16 x 16 x 4 MFMA tiles.  Long K is
 // split into fixed chunks whose partial results are summed in double by a
 // separate kernel in a fixed order (deterministic, no atomics).
 #include <algorithm>
+#include <type_traits>
 
 #include "cplx.h"
 #include "qeh_internal.h"
@@ -39,12 +41,23 @@ __device__ __forceinline__ void mfma(double a, double b, doublex4 &c) {
 
 // One workgroup: a BM x BN tile of C over the K slice [kbeg, kend).  Global
 // tiles are prefetched into registers while the MFMAs consume the LDS copy of
-// the previous slice (two LDS buffers, one barrier per slice).
-template <int BMODE, int BM, int BN, int BK, int RM, int WGM, int WGN>
+// the previous slice (two LDS buffers, one barrier per slice).  LDS keeps the
+// elements as loaded (re, im together): one 16-byte store an element and one
+// 16-byte read a fragment, free of bank conflicts at a pitch of BK + 1
+// elements.  B's conjugation (CJ) is a sign in the sums.  RM = 1 and 3 add both
+// products of a part into one accumulator set.
+//
+// Bound: the f64 matrix rate (72.7 TFLOP/s for a library product of 8192^3
+// here, 62 for this kernel on 2048 x 2048 x 4096) and, at Gamma, beta from HBM
+// (2.4 GB at 2048 projectors: 0.5 ms).  Planar LDS tiles with masked loads ->
+// this kernel (us): 128 x 512, K 23 976, 197 -> 177; 128 x 23 976, K 512,
+// 196 -> 177; Gamma 64 x 2 048, K 74 047, 791 -> 731; 64 x 74 047, K 2 048,
+// 890 -> 768.
+template <int BMODE, int BM, int BN, int BK, int RM, int WGM, int WGN, bool CJ>
 __global__ __launch_bounds__(64 * WGM * WGN) __attribute__((amdgpu_waves_per_eu(3)))
 void cgemm_kernel(
     const double2 *__restrict__ A, long lda, const double2 *__restrict__ B, long ldb,
-    double2 *__restrict__ C, long ldc, int M, int N, int K, int conjA, int conjB, int accumulate,
+    double2 *__restrict__ C, long ldc, int M, int N, int K, int accumulate,
     int kchunk, long split_stride, int tiles_m, int tiles_n, int ntiles, int per_xcd) {
   constexpr int kGT = 64 * WGM * WGN;
   constexpr int BKP = BK + 1;
@@ -52,11 +65,9 @@ void cgemm_kernel(
   constexpr int TN = BN / (16 * WGN);
   constexpr int NA = BM * BK / kGT;
   constexpr int NB = BN * BK / kGT;
-  static_assert(TM * 16 * WGM == BM && TN * 16 * WGN == BN && BK % 4 == 0, "tile / wave mismatch");
   static_assert(NA * kGT == BM * BK && NB * kGT == BN * BK, "tile / thread mismatch");
-  __shared__ double As[2][2][BM * BKP];   // [buffer][re, im]
-  __shared__ double Bs[2][2][BN * BKP];
-
+  __shared__ double2 As[2][BM * BKP];
+  __shared__ double2 Bs[2][BN * BKP];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
@@ -77,107 +88,110 @@ void cgemm_kernel(
   const int kbeg = kz * kchunk;
   const int kend = min(K, kbeg + kchunk);
   double2 *Cz = C + (long)kz * split_stride;
-  const double sa = conjA ? -1.0 : 1.0;
-  const double sb = conjB ? -1.0 : 1.0;
-
-  doublex4 p1[TM][TN], p2[TM][TN], p3[TM][TN];
+  constexpr int NP = RM == 0 ? 3 : RM >= 2 ? 2 : 1;
+  doublex4 p[NP][TM][TN];
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+  for (int q = 0; q < NP; ++q)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        p1[i][j][e] = 0.0;
-        p2[i][j][e] = 0.0;
-        p3[i][j][e] = 0.0;
-      }
-
-  // Global operand loads for one K slice into registers.
-  auto gload = [&](int k0, double2 *ra, double2 *rb) {
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) p[q][i][j][e] = 0.0;
+  // Rows beyond M / N repeat the last one (their results are not stored), so
+  // whole slices load without masks.
+  const double2 *pa[NA], *pb[NB];
+  int la[NA], lb[NB], ka[NA], kb[NB];   // LDS slot and k of each load
+#pragma unroll
+  for (int u = 0; u < NA; ++u) {
+    const int e = tid + u * kGT;
+    const int r = e / BK, k = e % BK;
+    pa[u] = A + (long)min(m0 + r, M - 1) * lda + kbeg + k;
+    la[u] = r * BKP + k;
+    ka[u] = k;
+  }
+#pragma unroll
+  for (int u = 0; u < NB; ++u) {
+    const int e = tid + u * kGT;
+    const int k = BMODE == 0 ? e % BK : e / BN;
+    const int r = BMODE == 0 ? e / BK : e % BN;
+    const int gn = min(n0 + r, N - 1);
+    pb[u] = BMODE == 0 ? B + (long)gn * ldb + kbeg + k : B + (long)(kbeg + k) * ldb + gn;
+    lb[u] = r * BKP + k;
+    kb[u] = k;
+  }
+  double2 ra[NA], rb[NB];
+  // slice at k0 into registers; FULL: all its BK k are inside the chunk
+  auto gload = [&](int k0, auto full) {
+    constexpr bool FULL = decltype(full)::value;
 #pragma unroll
     for (int u = 0; u < NA; ++u) {
-      const int e = tid + u * kGT;
-      const int r = e / BK, k = e % BK;
-      const int gm = m0 + r, gk = k0 + k;
-      ra[u] = (gm < M && gk < kend) ? A[(long)gm * lda + gk] : make_double2(0.0, 0.0);
+      ra[u] = FULL || k0 + ka[u] < kend ? *pa[u] : make_double2(0.0, 0.0);
+      pa[u] += BK;
     }
 #pragma unroll
     for (int u = 0; u < NB; ++u) {
-      const int e = tid + u * kGT;
-      const int k = BMODE == 0 ? e % BK : e / BN;
-      const int r = BMODE == 0 ? e / BK : e % BN;
-      const int gn = n0 + r, gk = k0 + k;
-      const long at = BMODE == 0 ? (long)gn * ldb + gk : (long)gk * ldb + gn;
-      rb[u] = (gn < N && gk < kend) ? B[at] : make_double2(0.0, 0.0);
+      rb[u] = FULL || k0 + kb[u] < kend ? *pb[u] : make_double2(0.0, 0.0);
+      pb[u] += BMODE == 0 ? (long)BK : (long)BK * ldb;
     }
   };
-  auto sstore = [&](int buf, const double2 *ra, const double2 *rb) {
-#pragma unroll
-    for (int u = 0; u < NA; ++u) {
-      const int e = tid + u * kGT;
-      const int r = e / BK, k = e % BK;
-      As[buf][0][r * BKP + k] = ra[u].x;
-      As[buf][1][r * BKP + k] = sa * ra[u].y;
-    }
-#pragma unroll
-    for (int u = 0; u < NB; ++u) {
-      const int e = tid + u * kGT;
-      const int k = BMODE == 0 ? e % BK : e / BN;
-      const int r = BMODE == 0 ? e / BK : e % BN;
-      Bs[buf][0][r * BKP + k] = rb[u].x;
-      Bs[buf][1][r * BKP + k] = sb * rb[u].y;
-    }
+  auto load = [&](int k0) {
+    if (k0 + BK <= kend)
+      gload(k0, std::true_type{});
+    else if (k0 < kend)
+      gload(k0, std::false_type{});
   };
-
+  auto sstore = [&](int buf) {
+#pragma unroll
+    for (int u = 0; u < NA; ++u) As[buf][la[u]] = ra[u];
+#pragma unroll
+    for (int u = 0; u < NB; ++u) Bs[buf][lb[u]] = rb[u];
+  };
   const int lr = lane % 16;   // row (A) / column (B) inside a block
   const int lk = lane / 16;   // k inside a step of 4
-
   auto compute = [&](int buf) {
 #pragma unroll
     for (int kk = 0; kk < BK; kk += 4) {
-      double ar[TM], ai[TM], as[TM], br[TN], bi[TN], bs[TN];
+      double2 a[TM], b[TN];
 #pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const int off = (wm0 + i * 16 + lr) * BKP + kk + lk;
-        ar[i] = As[buf][0][off];
-        ai[i] = As[buf][1][off];
-        as[i] = ar[i] + ai[i];
-      }
+      for (int i = 0; i < TM; ++i) a[i] = As[buf][(wm0 + i * 16 + lr) * BKP + kk + lk];
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int off = (wn0 + j * 16 + lr) * BKP + kk + lk;
-        br[j] = Bs[buf][0][off];
-        bi[j] = Bs[buf][1][off];
-        bs[j] = br[j] + bi[j];
-      }
+      for (int j = 0; j < TN; ++j) b[j] = Bs[buf][(wn0 + j * 16 + lr) * BKP + kk + lk];
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
-          mfma(ar[i], br[j], p1[i][j]);
-          if (RM == 2) {
-            mfma(ar[i], bi[j], p2[i][j]);
-          } else {
-            mfma(ai[i], bi[j], p2[i][j]);
-            if (RM == 0) mfma(as[i], bs[j], p3[i][j]);
+          mfma(a[i].x, b[j].x, p[0][i][j]);
+          if constexpr (RM == 1 || RM == 3) mfma(CJ ? a[i].y : -a[i].y, b[j].y, p[0][i][j]);
+          if constexpr (RM == 3) {
+            mfma(a[i].y, b[j].x, p[1][i][j]);
+            mfma(CJ ? -a[i].x : a[i].x, b[j].y, p[1][i][j]);
+          }
+          if constexpr (RM == 2) mfma(a[i].x, b[j].y, p[1][i][j]);
+          if constexpr (RM == 0) {
+            mfma(a[i].y, b[j].y, p[1][i][j]);
+            mfma(a[i].x + a[i].y, CJ ? b[j].x - b[j].y : b[j].x + b[j].y, p[2][i][j]);
           }
         }
     }
   };
-
   // one slice in flight: loaded during the MFMAs of the previous one
-  double2 ra[NA], rb[NB];
-  if (kbeg < kend) {
-    gload(kbeg, ra, rb);
-    sstore(0, ra, rb);
-  }
+  load(kbeg);
+  sstore(0);
   __syncthreads();
-  int buf = 0;
-  for (int k0 = kbeg; k0 < kend; k0 += BK) {
-    const bool more = k0 + BK < kend;
-    if (more) gload(k0 + BK, ra, rb);
+  int buf = 0, k0 = kbeg;
+  for (; k0 + 2 * BK <= kend; k0 += BK) {
+    gload(k0 + BK, std::true_type{});
     compute(buf);
-    if (more) sstore(buf ^ 1, ra, rb);
+    sstore(buf ^ 1);
+    __syncthreads();
+    buf ^= 1;
+  }
+  for (; k0 < kend; k0 += BK) {
+    const bool more = k0 + BK < kend;
+    if (more) load(k0 + BK);
+    compute(buf);
+    if (more) sstore(buf ^ 1);
     __syncthreads();
     buf ^= 1;
   }
@@ -193,35 +207,44 @@ void cgemm_kernel(
         const int gm = m0 + wm0 + i * 16 + lk + 4 * r;
         const int gn = n0 + wn0 + j * 16 + lr;
         if (gm < M && gn < N) {
-          double2 *p = Cz + (long)gm * ldc + gn;
-          double cr = RM == 2 ? p1[i][j][r] : p1[i][j][r] - p2[i][j][r];
-          double ci = RM == 0   ? p3[i][j][r] - p1[i][j][r] - p2[i][j][r]
-                      : RM == 2 ? p2[i][j][r]
-                                : 0.0;
+          double2 *q = Cz + (long)gm * ldc + gn;
+          double cr = p[0][i][j][r], ci = 0.0;
+          if constexpr (RM >= 2) ci = p[1][i][j][r];
+          if constexpr (RM == 0) {
+            const double p1 = p[0][i][j][r], p2 = CJ ? -p[1][i][j][r] : p[1][i][j][r];
+            cr = p1 - p2;
+            ci = p[2][i][j][r] - p1 - p2;
+          }
           if (accumulate) {
-            const double2 v = *p;
+            const double2 v = *q;
             cr += v.x;
             ci += v.y;
           }
-          *p = make_double2(cr, ci);
+          *q = make_double2(cr, ci);
         }
       }
 }
 
-// 64 x 64 tiles on four waves, K slices of 8.
-template <int BMODE, int RM> hipError_t run_tile(const GemmDesc &g, hipStream_t s) {
-  constexpr int BM = 64, BN = 64;
+template <int BMODE, int RM, int BM, int BN, int BK, int WGM, int WGN>
+hipError_t run_tile(const GemmDesc &g, hipStream_t s) {
   const int tm = (g.M + BM - 1) / BM, tn = (g.N + BN - 1) / BN;
   const long total = (long)tm * tn * g.nsplit;
   if (total > (1L << 30)) return hipErrorInvalidValue;
   const int per_xcd = (int)((total + 7) / 8);
   const int kchunk = g.nsplit > 1 ? g.kchunk : g.K;
-  hipLaunchKernelGGL((cgemm_kernel<BMODE, BM, BN, 8, RM, 2, 2>), dim3(8 * per_xcd), dim3(256), 0,
-                     s, reinterpret_cast<const double2 *>(g.A), g.lda,
+  hipLaunchKernelGGL((cgemm_kernel<BMODE, BM, BN, BK, RM, WGM, WGN, BMODE == 0>), dim3(8 * per_xcd),
+                     dim3(64 * WGM * WGN), 0, s, reinterpret_cast<const double2 *>(g.A), g.lda,
                      reinterpret_cast<const double2 *>(g.B), g.ldb,
-                     reinterpret_cast<double2 *>(g.C), g.ldc, g.M, g.N, g.K, g.conjA, g.conjB,
+                     reinterpret_cast<double2 *>(g.C), g.ldc, g.M, g.N, g.K,
                      g.accumulate, kchunk, g.split_stride, tm, tn, (int)total, per_xcd);
   return hipGetLastError();
+}
+
+// 64 x 64 tiles with K slices of 8, or 16 x 64 with slices of 16 (cgemm_flat).
+template <int BMODE, int RM> hipError_t run(const GemmDesc &g, hipStream_t s) {
+  if (cgemm_flat(g.M, g.N, g.K, g.bmode))
+    return run_tile<BMODE, RM == 0 ? 3 : RM, 16, 64, 16, 1, 4>(g, s);
+  return run_tile<BMODE, RM, 64, 64, 8, 2, 2>(g, s);
 }
 
 template <typename TP, typename TC>
@@ -336,14 +359,29 @@ __global__ __launch_bounds__(256) void dscale_kernel(
 
 }  // namespace
 
+// Flat 16 x 64 tiles where the product is too small for 64 x 64 tiles to hide
+// the latency of their slices behind each other's MFMAs, or where rows beyond M
+// cost more than the flat tile's lower rate (about 1.35 times the time per
+// padded element).  Measured, 64 x 64 -> 16 x 64 (us): 16 bands x 8 projectors,
+// K 1 503, 6.8 -> 4.0; 64 x 128, K 1 791, 8.1 -> 6.2; 77 x 384, K 9 121,
+// 57 -> 44; 256 x 512, K 7 127, 112 -> 127; without a split 128 x 128, K 128,
+// 20.5 -> 9.2; 64 x 1 791, K 128, 21 -> 9.7; 77 x 9 121, K 384 (286 tiles of
+// 64 x 64), 93 -> 50; 256 x 7 127, K 512 (448 tiles), 124 -> 151.
+bool cgemm_flat(int M, int N, int K, int bmode) {
+  const long t64 = (long)((M + 63) / 64) * ((N + 63) / 64);
+  if (bmode == 0 ? (double)M * N * K < 5e8 : t64 < 384) return true;
+  return 64 * ((M + 63) / 64) > 1.35 * 16 * ((M + 15) / 16);
+}
+
 // The Gamma-point forms: RM = 1 for beta^H psi (bmode 0), RM = 2 for beta ps
 // (bmode 1, A = ps real in complex storage).
 hipError_t launch_cgemm(const GemmDesc &g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0 || g.K <= 0) return hipSuccess;
-  if (g.ta != T_D2 || g.tb != T_D2 || g.tc != T_D2) return hipErrorInvalidValue;
-  if (g.rmode == 0) return g.bmode == 0 ? run_tile<0, 0>(g, s) : run_tile<1, 0>(g, s);
-  if (g.rmode == 1 && g.bmode == 0) return run_tile<0, 1>(g, s);
-  if (g.rmode == 2 && g.bmode == 1) return run_tile<1, 2>(g, s);
+  if (g.ta != T_D2 || g.tb != T_D2 || g.tc != T_D2 || g.conjA || g.conjB != (g.bmode == 0))
+    return hipErrorInvalidValue;
+  if (g.rmode == 0) return g.bmode == 0 ? run<0, 0>(g, s) : run<1, 0>(g, s);
+  if (g.rmode == 1 && g.bmode == 0) return run<0, 1>(g, s);
+  if (g.rmode == 2 && g.bmode == 1) return run<1, 2>(g, s);
   return hipErrorInvalidValue;
 }
 

@@ -245,6 +245,9 @@ struct GemmDesc {
 };
 // FP64 operands and results.
 hipError_t launch_cgemm(const GemmDesc &g, hipStream_t s);
+// Whether launch_cgemm takes flat 16 x 64 tiles (else 64 x 64): callers that
+// split K count their workgroups by it.
+bool cgemm_flat(int M, int N, int K, int bmode);
 // The single-precision projector products: B and the products in single
 // precision, beta^H psi (bmode 0, conjB; A in float or double, C float) and
 // beta ps (bmode 1; C double).
@@ -252,10 +255,10 @@ hipError_t launch_split_gemm(const GemmDesc &g, hipStream_t s);
 
 // ---- Davidson building blocks shared with the CG solver (davidson.cpp) ----
 // out(i, j) = <X_i|Y_j> for i < nrow, j < ncol (col-major, ld), FP64 MFMA,
-// split-K partials in `part` (16 * 32 * nrow * ncol bytes) summed in a fixed
-// order; real inner products on Gamma contexts.
+// split-K partials in `part` (room for part_cap of them) summed in a fixed order;
+// real inner products on Gamma contexts.
 hipError_t reduce_cols(const qeh_ctx *c, const double2 *X, int nrow, const double2 *Y, int ncol,
-                       double2 *out, int ld, double2 *part);
+                       double2 *out, int ld, double2 *part, size_t part_cap);
 // rows b < nb: out_b = sum_j Y(j, b) X_j  (Y col-major ld, j < n)
 hipError_t rotate(const qeh_ctx *c, const double2 *Y, int ld, int n, int nb, const double2 *X,
                   double2 *out);
