@@ -324,6 +324,8 @@ hipError_t launch_dscale(const qeh_ctx *c, int nbk, const double2 *psi, long ldp
 // ---- dense Hermitian subspace solver (eigh_kernels.hip) --------------------
 // Reduced problems up to kEigMaxN; column-major double2 matrices.
 constexpr int kEigMaxN = 2048;
+// Orders that the one-workgroup kernels of eigh_small.hip hold in registers.
+constexpr int kEigRegN = 128;
 // Largest basis for which the Davidson's automatic choice takes the own solver:
 // above it the one-stage Householder reduction streams the trailing matrix
 // from HBM at every step (n = 2048: 86 ms per complex solve) and rocSOLVER's
@@ -338,6 +340,16 @@ constexpr int kEigAutoMaxN = 1024;
 // doubles of scratch (the eigenpair scratch below is large enough and free).
 hipError_t launch_chol(double2 *S, long ld, int n, int *info, double *scr, bool wide,
                        hipStream_t s);
+// The same and the tridiagonalisation for orders <= kEigRegN (eigh_small.hip).
+hipError_t launch_chol_reg(double2 *S, long ld, int n, int *info, hipStream_t s);
+hipError_t launch_tridiag_reg(double2 *A, long lda, int m, double *d, double *e, double2 *tau,
+                              const int *info_chol, hipStream_t s);
+// launch_trsm and launch_backtr (below) for orders <= 256.
+hipError_t launch_trsm_small(int mode, const double2 *T, long ldt, int n, const double2 *B,
+                             long ldb, int ncol, double2 *X, long ldx, hipStream_t s);
+hipError_t launch_backtr_small(const double2 *A, long lda, int n, const double *tri,
+                               const double *Zt, int ldz, int nb, double2 *Zc, long ldc,
+                               const int *info_chol, const int *info_eig, hipStream_t s);
 // X = L^-1 B (mode 0, T = L lower), X = L^-1 M^H with B = M (mode 1), or
 // X = U^-1 B (mode 2, T = U upper, backward); ncol columns, one wave each.
 hipError_t launch_trsm(int mode, const double2 *T, long ldt, int n, const double2 *B, long ldb,
