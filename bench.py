@@ -129,7 +129,8 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hpsi_c5_gamma_hbm_traffic.json")
 # passes, the projector GEMMs and D scaling, the Gamma unpack) and the headers
 # they include
 HPSI_SOURCES = ("cplx.h", "dav_kernels.hip", "fft_kernels.hip", "fft_reg.h", "gemm_kernels.hip",
-                "plane2.h", "plane2_f32.hip", "plane2_f64.hip", "qeh_internal.h", "split_gemm.hip")
+                "plane2.h", "plane2_f32.hip", "plane2_f64.hip", "qeh_internal.h", "split_gemm.hip",
+                "stick2.h", "stick2_f32.hip", "stick2_f64.hip")
 
 
 def kernel_source_hash():

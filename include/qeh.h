@@ -490,7 +490,8 @@ qeh_status qeh_server_destroy(qeh_server *srv);
 /* Shape facts of a context: [npw, nst, nkb, N1, N2, N3, x-extent, block,
  * precision, plane path (0 one kernel, 1 split through HBM; 2 and 4: one
  * kernel, on a box whose density runs the lane-pair / lane-quad passes),
- * stick path (0 LDS passes, 1 lane-pair register z transforms), projector
+ * stick path (1 in the mixed form with N3 = 16, 18, 20, 24, 30, 32, 36, 40, 48,
+ * 50, 54, 60, 64, 72, 80 or 90, else 0), projector
  * tiles (0 the 64-row MFMA tiles, 1 the wide single-precision tiles:
  * QEH_MIXED with >= 2048 projectors and a block of >= 128 bands)].  out has
  * room for n values (up to 12).
@@ -499,8 +500,8 @@ qeh_status qeh_server_destroy(qeh_server *srv);
  * most 16, and 125) whose x-extent columns fit in LDS, else LDS passes of
  * small radices.  Environment variables read by qeh_ctx_plan / qeh_ctx_create:
  * QEH_FORCE_SPLIT_PLANE=1 forces the split path (a test hook);
- * QEH_STICK_KERNEL=generic keeps the LDS-pass z transforms where the lane-pair
- * ones would run (mixed form, N3 a compiled size; a test hook);
+ * QEH_STICK_KERNEL=generic keeps the LDS-pass z transforms where the two-factor
+ * ones would run (N3 a compiled size; a test hook);
  * QEH_PLANE_KERNEL=generic keeps the LDS-pass plane kernel where the two-factor
  * one would run (a test and comparison hook); QEH_PLANE_ROWS=n caps the rows
  * the LDS-pass plane kernel expands at once (a tuning knob; fewer rows use

@@ -17,9 +17,10 @@ CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libqeh.so")
 BUILD = os.path.join(ROOT, "_build")
 
-HIP_SOURCES = ["fft_kernels.hip", "plane2_f32.hip", "plane2_f64.hip", "gemm_kernels.hip",
-               "split_gemm.hip", "dav_kernels.hip", "beta_kernels.hip", "eigh_kernels.hip",
-               "eigh_small.hip", "eigh_tri.hip", "cg_kernels.hip"]
+HIP_SOURCES = ["fft_kernels.hip", "plane2_f32.hip", "plane2_f64.hip", "stick2_f32.hip",
+               "stick2_f64.hip", "gemm_kernels.hip", "split_gemm.hip", "dav_kernels.hip",
+               "beta_kernels.hip", "eigh_kernels.hip", "eigh_small.hip", "eigh_tri.hip",
+               "cg_kernels.hip"]
 CPP_SOURCES = ["ctx.cpp", "davidson.cpp", "server.cpp", "beta.cpp", "cg.cpp"]
 
 COMMON = ["-O3", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-function",

@@ -108,6 +108,7 @@ namespace {
 struct HostMaps {
   int nst = 0, hmin = 0, ext = 0;
   int kmin = 0, kmax = 0;
+  int lmin = 0, lmax = 0;   // of l over the sphere
   int npw_fft = 0;                  // G-vectors the FFT path places (the full sphere)
   std::vector<int> stick_off, stick_h, stick_k;
   std::vector<int> full;            // Gamma cells: the full sphere's Miller list
@@ -204,6 +205,8 @@ qeh_status validate(const qeh_cell *c, HostMaps *hm) {
   hm->nst = (int)hm->stick_h.size();
   hm->hmin = lo[0];
   hm->ext = hi[0] - lo[0] + 1;
+  hm->lmin = lo[2];
+  hm->lmax = hi[2];
   hm->kmin = lo[1];
   hm->kmax = hi[1];
   // finiteness of the numeric inputs
@@ -266,12 +269,13 @@ size_t bump(size_t *cur, size_t bytes) {
 }
 
 struct Geometry {
-  int nkb, nd, nchunk, nsplit, kchunk, plane_path, zpair, wide, ldb;
+  int nkb, nd, nchunk, nsplit, kchunk, plane_path, stick_path, wide, ldb;
   FftDim dx, dy, dz;
   PlaneGeom pg;
   SplitGeom spg;
   StickGeom sg;
   TwoGeom two;
+  StickTwoGeom st2;
 };
 
 void geometry(const qeh_cell *c, const HostMaps &hm, Geometry *g) {
@@ -355,12 +359,16 @@ void geometry(const qeh_cell *c, const HostMaps &hm, Geometry *g) {
                       : quad_plane_supported(prec, n1, n2) ? 4
                                                            : 0;
   }
-  // lane-pair K1 / K3 (single precision, N3 with a compiled form);
-  // QEH_STICK_KERNEL=generic keeps the LDS-pass kernels (test hook)
-  g->zpair = 0;
-  if (pair_z_supported(prec, n3) && pair_z_lds_bytes(n3) <= (size_t)kLdsMax) {
+  // two-factor K1 / K3 at the compiled N3; QEH_STICK_KERNEL=generic keeps the
+  // LDS-pass kernels (test hook)
+  g->st2 = StickTwoGeom{};
+  g->stick_path = 0;
+  {
     const char *kern = std::getenv("QEH_STICK_KERNEL");
-    if (!(kern && std::strcmp(kern, "generic") == 0)) g->zpair = 1;
+    if (!(kern && std::strcmp(kern, "generic") == 0)) {
+      stick_two_geometry(prec, n3, hm.lmin, hm.lmax, &g->st2);
+      g->stick_path = pair_plane_supported(prec, n3, n3) ? 1 : 0;
+    }
   }
   g->pg.ext_div = make_fastdiv(hm.ext);
   g->pg.rc_div = make_fastdiv(g->pg.rc);
@@ -448,8 +456,9 @@ Layout layout(const qeh_cell *c, const HostMaps &hm, const Geometry &g) {
   L.off_psi32 = bump(&cur, c->precision == QEH_MIXED ? 8 * (size_t)c->block * g.ldb : 0);
   // projectors built on the device: the generator's staging area
   L.off_pgen = bump(&cur, g.nkb > 0 && !c->beta ? projgen_layout(c).total : 0);
-  // Gamma: the full-sphere H of the band pairs (FP64), written by K3
-  L.off_gbuf = bump(&cur, c->gamma ? 16 * (size_t)((c->block + 1) / 2) * hm.npw_fft : 0);
+  // Gamma, LDS-pass K3: the full-sphere H of the band pairs (FP64)
+  L.off_gbuf =
+      bump(&cur, c->gamma && !g.st2.on ? 16 * (size_t)((c->block + 1) / 2) * hm.npw_fft : 0);
   L.total = cur;
   return L;
 }
@@ -544,7 +553,7 @@ qeh_status qeh_ctx_create(const qeh_cell *cell, void *arena, size_t arena_bytes,
   c->block = cell->block;
   c->prec = cell->precision;
   c->plane_path = g.plane_path;
-  c->zpair = g.zpair;
+  c->stick_path = g.stick_path;
   c->nsplit = g.nsplit;
   c->wide = g.wide;
   c->ldb = g.ldb;
@@ -557,6 +566,7 @@ qeh_status qeh_ctx_create(const qeh_cell *cell, void *arena, size_t arena_bytes,
   c->spg = g.spg;
   c->sg = g.sg;
   c->two = g.two;
+  c->st2 = g.st2;
   c->stream = reinterpret_cast<hipStream_t>(hip_stream);
   c->arena = reinterpret_cast<char *>(arena);
   c->arena_bytes = arena_bytes;
@@ -585,7 +595,7 @@ qeh_status qeh_ctx_create(const qeh_cell *cell, void *arena, size_t arena_bytes,
   c->d.big = g.plane_path == 1 ? A + L.off_big : nullptr;
   c->d.colstart = reinterpret_cast<int *>(A + L.off_colstart);
   c->d.psi32 = c->prec == QEH_MIXED ? reinterpret_cast<float2 *>(A + L.off_psi32) : nullptr;
-  c->d.gbuf = c->gamma ? reinterpret_cast<double2 *>(A + L.off_gbuf) : nullptr;
+  c->d.gbuf = c->gamma && !g.st2.on ? reinterpret_cast<double2 *>(A + L.off_gbuf) : nullptr;
 
   const int npw = cell->npw, n1 = c->n1, n2 = c->n2, n3 = c->n3;
   const size_t nfft = (size_t)n1 * n2 * n3;
@@ -594,9 +604,11 @@ qeh_status qeh_ctx_create(const qeh_cell *cell, void *arena, size_t arena_bytes,
   std::vector<int> gmap(hm.npw_fft), tidx(hm.nst), tidx_dit(hm.nst), tidx2, xin(n1, -1);
   const int *mf = hm.miller_fft;
   for (int s = 0; s < hm.nst; ++s) {
-    for (int gg = hm.stick_off[s]; gg < hm.stick_off[s + 1]; ++gg)
-      gmap[gg] = s * c->sg.ldz + (c->zpair ? imod(mf[3 * gg + 2], n3)
-                                           : fft_digit_pos(c->dz, imod(mf[3 * gg + 2], n3)));
+    for (int gg = hm.stick_off[s]; gg < hm.stick_off[s + 1]; ++gg) {
+      const int l = imod(mf[3 * gg + 2], n3);
+      gmap[gg] = c->st2.on ? s * c->st2.ldz + l / c->st2.b * c->st2.bp + l % c->st2.b
+                           : s * c->sg.ldz + fft_digit_pos(c->dz, l);
+    }
     const int ky = imod(hm.stick_k[s], n2);
     tidx_dit[s] = (hm.stick_h[s] - hm.hmin) * c->pg.ldT + fft_digit_pos(c->dy, ky);
     tidx[s] = (c->plane_path == 2 || c->plane_path == 4) ? (hm.stick_h[s] - hm.hmin) * c->pg.ldT + ky
@@ -799,8 +811,7 @@ qeh_status apply_block(qeh_ctx *c, int part, int nbk, const double2 *psi, int ld
   if ((part == 0 || part == 2) && c->gamma) {
     // Gamma: bands 2p, 2p+1 go through one complex FFT as psi_2p + i psi_2p+1
     // over the full sphere (K1 reads the pairs from the stored halves; K3
-    // writes the full-sphere result to gbuf), and are separated again with the
-    // kinetic term added
+    // separates them again)
     const int np = (nbk + 1) / 2;
     {
       StageGuard g(c, 0);
@@ -814,10 +825,7 @@ qeh_status apply_block(qeh_ctx *c, int part, int nbk, const double2 *psi, int ld
     if (e != hipSuccess) return hip_fail(e, "K2 launch");
     {
       StageGuard g(c, 2);
-      e = launch_k3(c, np, c->d.gbuf, c->npw_fft, c->d.gbuf, c->npw_fft, 0);
-      if (e == hipSuccess)
-        e = launch_gamma_unpack(c->d.gbuf, c->npw_fft, nbk, c->npw, psi, ldpsi, c->d.kin, hpsi,
-                                ldh, c->stream);
+      e = launch_k3(c, nbk, psi, ldpsi, hpsi, ldh);
     }
     if (e != hipSuccess) return hip_fail(e, "K3 launch");
   } else if (part == 0 || part == 2) {
@@ -833,7 +841,7 @@ qeh_status apply_block(qeh_ctx *c, int part, int nbk, const double2 *psi, int ld
     if (e != hipSuccess) return hip_fail(e, "K2 launch");
     {
       StageGuard g(c, 2);
-      e = launch_k3(c, nbk, psi, ldpsi, hpsi, ldh, 1);
+      e = launch_k3(c, nbk, psi, ldpsi, hpsi, ldh);
     }
     if (e != hipSuccess) return hip_fail(e, "K3 launch");
   }
@@ -1179,7 +1187,7 @@ qeh_status qeh_ctx_hdiag(const qeh_ctx *c, double *hdiag) {
 qeh_status qeh_ctx_info(const qeh_ctx *c, long *out, int n) {
   if (!c || !out) return invalid("null argument");
   const long v[12] = {c->npw, c->nst, c->nkb, c->n1, c->n2, c->n3, c->ext, c->block, c->prec,
-                      c->plane_path, c->zpair, c->wide};
+                      c->plane_path, c->stick_path, c->wide};
   for (int i = 0; i < n && i < 12; ++i) out[i] = v[i];
   return QEH_OK;
 }

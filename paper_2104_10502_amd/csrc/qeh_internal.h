@@ -65,6 +65,13 @@ struct TwoGeom {
   size_t lds;
 };
 
+// Two-factor K1 / K3 (stick2.h): whether they run, 2^sl sticks per workgroup,
+// line pitch, the split of a z position p into slot (p / b) * bp + p % b.
+struct StickTwoGeom {
+  int on, half, sl, ldz, b, bp;
+  size_t lds;
+};
+
 struct StickGeom {
   int ldz;   // z-line stride (>= N3, odd)
   int S;     // sticks per workgroup
@@ -75,8 +82,8 @@ struct StickGeom {
 // Device arrays of one context, all inside the caller's arena.
 struct DevMaps {
   int *stick_off;    // [nst+1] first G of each stick
-  int *gmap;         // [npw] s*ldz + digit-reversed z position (natural z for the
-                     // lane-pair K1 / K3, whose ldz is N3 | 1 as well)
+  int *gmap;         // [npw] s*ldz + digit-reversed z position (two-factor K1 / K3:
+                     // s * their pitch + slot)
   int *tidx;         // [nst] plane-tile index c*ldT + pos_y(k mod N2); the lane-pair
                      // and lane-quad density passes take natural y (pos_y = identity)
   int *tidx2;        // [nst] the same for the two-factor plane kernel (y shifted to k - kmin)
@@ -99,7 +106,8 @@ struct DevMaps {
                      // single-precision Gamma contexts)
   float2 *psi32;     // mixed form: [block][ldb] single-precision copy of psi (K1)
   void *big;         // split plane path: [block][N3][ext][N2] (or null)
-  double2 *gbuf;     // Gamma: [(block+1)/2][npw_fft] full-sphere H of band pairs (or null)
+  double2 *gbuf;     // Gamma, LDS-pass K3: [(block+1)/2][npw_fft] full-sphere H of band
+                     // pairs (or null)
   int *colstart;     // [ext+1] first stick of each x-extent column
 };
 
@@ -114,7 +122,7 @@ struct qeh_ctx {
   int block = 0, prec = 0;
   int plane_path = 0;   // 0 one kernel, 1 split through HBM; 2, 4: one kernel, natural-order
                         // y tables for the lane-pair / lane-quad density passes
-  int zpair = 0;        // 1: lane-pair K1 / K3 (gmap at natural z)
+  int stick_path = 0;   // as reported: 1 for single-precision N3 of a lane-pair size
   int nsplit = 1, kchunk = 0;
   int wide = 0;         // 1: wide single-precision tiles for the projector products
   int ldb = 0;          // row length of beta and psi32 (npw; single precision: padded to
@@ -125,6 +133,7 @@ struct qeh_ctx {
   qeh::SplitGeom spg{};
   qeh::StickGeom sg{};
   qeh::TwoGeom two{};
+  qeh::StickTwoGeom st2{};
   int tw_off[3] = {0, 0, 0};
   hipStream_t stream = nullptr;
   qeh::DevMaps d{};
@@ -156,16 +165,28 @@ hipError_t launch_k1(const qeh_ctx *c, int nbk, const double2 *psi, int ldpsi);
 hipError_t launch_k1_gamma(const qeh_ctx *c, int nbk, const double2 *psi, int ldpsi,
                            const int2 *pairs = nullptr, int npairs = 0, bool copy32 = false);
 hipError_t launch_k2(const qeh_ctx *c, int nbk);
-hipError_t launch_k3(const qeh_ctx *c, int nbk, const double2 *psi, int ldpsi,
-                     double2 *hpsi, int ldh, int add_kinetic);
+// H psi of a block of nbk bands, local part, with the kinetic term.
+hipError_t launch_k3(const qeh_ctx *c, int nbk, const double2 *psi, int ldpsi, double2 *hpsi,
+                     int ldh);
+// The two-factor forms (stick2_f32.hip, stick2_f64.hip): K1 of np bands or Gamma
+// pairs (nbk, pairs: as in launch_k1_gamma); K3 as launch_k3.
+hipError_t launch_k1_two_f32(const qeh_ctx *c, int np, const double2 *psi, int ldpsi, int nbk,
+                             const int2 *pairs, float2 *psi32);
+hipError_t launch_k1_two_f64(const qeh_ctx *c, int np, const double2 *psi, int ldpsi, int nbk,
+                             const int2 *pairs, float2 *psi32);
+hipError_t launch_k3_two_f32(const qeh_ctx *c, int nbk, const double2 *psi, int ldpsi,
+                             double2 *hpsi, int ldh);
+hipError_t launch_k3_two_f64(const qeh_ctx *c, int nbk, const double2 *psi, int ldpsi,
+                             double2 *hpsi, int ldh);
+// Their geometry for lines of n3 points holding l in [lmin, lmax]; false if n3
+// is not a compiled size.
+bool stick_two_geometry(int prec, int n3, int lmin, int lmax, StickTwoGeom *g);
 size_t plane_lds_bytes(int prec, int ext, int n1, int n2, const PlaneGeom &g);
 size_t stick_lds_bytes(int prec, int n3, const StickGeom &g);
 // Square boxes whose density passes are the lane-pair (single precision) or
-// lane-quad (FP64) kernels; lane-pair z transforms for N3.
+// lane-quad (FP64) kernels.
 bool pair_plane_supported(int prec, int n1, int n2);
-bool pair_z_supported(int prec, int n3);
 bool quad_plane_supported(int prec, int n1, int n2);
-size_t pair_z_lds_bytes(int n3);
 
 // Two-factor plane kernel: geometry for an x-extent of ext columns and a y
 // extent of exty (false: no compiled form, or the columns exceed LDS).
