@@ -199,9 +199,9 @@ qeh_status qeh_apply_h_part(qeh_ctx *ctx, int part, int nb, const double *psi,
  * Bands go through in blocks of the context's block size: K1 (sticks and
  * inverse z), inverse y columns into the workspace, then inverse x rows with
  * the occupation-weighted |psi|^2 summed in double in a fixed order (the
- * result does not depend on timing).  Contexts on the register plane
- * kernels (lane pairs in the mixed form, lane quads in FP64) run the y and x
- * transforms as one fused pass per z plane instead (no column workspace);
+ * result does not depend on timing).  Contexts on the two-factor plane kernel
+ * run the y and x transforms as one fused pass per z plane instead (no column
+ * workspace; N1 = N2 up to 120 in FP64 and 160 in the mixed form, most sizes);
  * QEH_DENSITY_KERNEL=rows or =generic, read per call, selects the unfused
  * lane-pair rows or the LDS-pass rows (test hooks).  Precision: the
  * context's (the mixed form transforms in FP32 and sums in FP64).  Blocking: returns after the

@@ -256,7 +256,7 @@ qeh_status validate(const qeh_cell *c, HostMaps *hm) {
 
 // Arena layout, shared by plan and create.
 struct Layout {
-  size_t off_stick_off, off_gmap, off_tidx, off_tidx_dit, off_xin, off_kin, off_hdiag, off_vs,
+  size_t off_stick_off, off_gmap, off_tidx, off_xin, off_kin, off_hdiag, off_vs,
       off_tidx2, off_tw, off_beta, off_dmat, off_qmat, off_pj0, off_pnb, off_pdoff, off_chunk, off_sbuf, off_part,
       off_ps, off_big, off_colstart, off_psi32, off_pgen, off_gbuf;
   size_t total;
@@ -346,8 +346,8 @@ void geometry(const qeh_cell *c, const HostMaps &hm, Geometry *g) {
   }
   // two-factor kernel (square planes of a compiled size whose columns fit in
   // LDS): faster than the LDS-pass and the split kernels at every size measured
-  // (1.5 to 4.2 times, 12 .. 180).  Plane paths 2 and 4 name the sizes whose
-  // density passes take natural-order y tables.  QEH_PLANE_KERNEL=generic and
+  // (1.5 to 4.2 times, 12 .. 180).  Plane paths 2 and 4 are what the reports
+  // call the boxes of the lane-pair and lane-quad sizes.  QEH_PLANE_KERNEL=generic and
   // QEH_FORCE_SPLIT_PLANE=1 keep the LDS-pass kernels (test hooks).
   g->two = TwoGeom{};
   {
@@ -432,7 +432,6 @@ Layout layout(const qeh_cell *c, const HostMaps &hm, const Geometry &g) {
   L.off_stick_off = bump(&cur, 4 * (hm.nst + 1));
   L.off_gmap = bump(&cur, 4 * (size_t)hm.npw_fft);
   L.off_tidx = bump(&cur, 4 * (size_t)hm.nst);
-  L.off_tidx_dit = bump(&cur, 4 * (size_t)hm.nst);
   L.off_tidx2 = bump(&cur, g.two.on ? 4 * (size_t)hm.nst : 0);
   L.off_xin = bump(&cur, 4 * (size_t)c->fft[0]);
   L.off_kin = bump(&cur, 8 * (size_t)c->npw);
@@ -574,7 +573,6 @@ qeh_status qeh_ctx_create(const qeh_cell *cell, void *arena, size_t arena_bytes,
   c->d.stick_off = reinterpret_cast<int *>(A + L.off_stick_off);
   c->d.gmap = reinterpret_cast<int *>(A + L.off_gmap);
   c->d.tidx = reinterpret_cast<int *>(A + L.off_tidx);
-  c->d.tidx_dit = reinterpret_cast<int *>(A + L.off_tidx_dit);
   c->d.tidx2 = g.two.on ? reinterpret_cast<int *>(A + L.off_tidx2) : nullptr;
   c->d.xin = reinterpret_cast<int *>(A + L.off_xin);
   c->d.kin = reinterpret_cast<double *>(A + L.off_kin);
@@ -601,7 +599,7 @@ qeh_status qeh_ctx_create(const qeh_cell *cell, void *arena, size_t arena_bytes,
   const size_t nfft = (size_t)n1 * n2 * n3;
   const bool f64 = c->prec == QEH_FP64;
   // ---- host-side maps
-  std::vector<int> gmap(hm.npw_fft), tidx(hm.nst), tidx_dit(hm.nst), tidx2, xin(n1, -1);
+  std::vector<int> gmap(hm.npw_fft), tidx(hm.nst), tidx2, xin(n1, -1);
   const int *mf = hm.miller_fft;
   for (int s = 0; s < hm.nst; ++s) {
     for (int gg = hm.stick_off[s]; gg < hm.stick_off[s + 1]; ++gg) {
@@ -610,9 +608,7 @@ qeh_status qeh_ctx_create(const qeh_cell *cell, void *arena, size_t arena_bytes,
                            : s * c->sg.ldz + fft_digit_pos(c->dz, l);
     }
     const int ky = imod(hm.stick_k[s], n2);
-    tidx_dit[s] = (hm.stick_h[s] - hm.hmin) * c->pg.ldT + fft_digit_pos(c->dy, ky);
-    tidx[s] = (c->plane_path == 2 || c->plane_path == 4) ? (hm.stick_h[s] - hm.hmin) * c->pg.ldT + ky
-                                                          : tidx_dit[s];
+    tidx[s] = (hm.stick_h[s] - hm.hmin) * c->pg.ldT + fft_digit_pos(c->dy, ky);
   }
   if (c->two.on) {
     tidx2.resize(hm.nst);
@@ -708,7 +704,6 @@ qeh_status qeh_ctx_create(const qeh_cell *cell, void *arena, size_t arena_bytes,
   up(c->d.stick_off, hm.stick_off.data(), 4 * hm.stick_off.size());
   up(c->d.gmap, gmap.data(), 4 * gmap.size());
   up(c->d.tidx, tidx.data(), 4 * tidx.size());
-  up(c->d.tidx_dit, tidx_dit.data(), 4 * tidx_dit.size());
   if (c->two.on) up(c->d.tidx2, tidx2.data(), 4 * tidx2.size());
   up(c->d.xin, xin.data(), 4 * xin.size());
   up(c->d.colstart, colstart.data(), 4 * colstart.size());

@@ -582,155 +582,6 @@ __global__ __launch_bounds__(kRT) __attribute__((amdgpu_waves_per_eu(2))) void k
   for (int k = 0; k < M; ++k) out[k] = acc[k];
 }
 
-// Fused density plane pass on lane pairs (mixed form, N1 = N2 = N a compiled
-// size, lane-pair plane tables): one workgroup = one z plane x one subgroup of
-// bands.  Per band: the plane's sticks into the LDS column tile (natural y),
-// inverse y transforms of the x-extent columns, then the x rows, each held by
-// the same pair (y, l) for every band, whose N/2 points accumulate
-// occ_b |psi_b|^2 in double registers (the x shift of the rows is a unit-modulus
-// phase).  No HBM round trip between the column and row transforms.
-template <int N>
-__global__ __launch_bounds__(kRT) __attribute__((amdgpu_waves_per_eu(2))) void k2d_plane_pair(
-    const float2 *__restrict__ sbuf, const double *__restrict__ occ, double *__restrict__ partial,
-    const int *__restrict__ tidx, int nst, int n3, int ext, int nbk, int bsub) {
-  constexpr int LD = N | 1, M = N / 2;
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  float2 *T = reinterpret_cast<float2 *>(smem_raw);
-  const int tile = ext * LD;
-  const float2 *zslot = T + tile;
-  const int z = blockIdx.x % n3;
-  const int sub = blockIdx.x / n3;
-  const int b0 = sub * bsub;
-  const int b1 = min(nbk, b0 + bsub);
-  const int tid = threadIdx.x;
-  const float2 zero = make_float2(0.f, 0.f);
-  if (tid == 0) T[tile] = zero;
-  const bool row_lane = tid < 2 * N;
-  const bool odd = tid & 1;
-  const int l = odd ? 1 : 0;
-  const int y = tid >> 1;
-  double acc[M];
-#pragma unroll
-  for (int k = 0; k < M; ++k) acc[k] = 0.0;
-  for (int b = b0; b < b1; ++b) {
-    for (int i = tid; i < tile; i += kRT) T[i] = zero;
-    __syncthreads();
-    const float2 *plane = sbuf + ((size_t)b * n3 + z) * nst;
-    for (int s = tid; s < nst; s += kRT) T[tidx[s]] = plane[s];
-    __syncthreads();
-    for (int j = tid; j < 2 * ext; j += kRT) {
-      const bool jodd = j & 1;
-      float2 *col = T + (j >> 1) * LD;
-      float2 v[M];
-#pragma unroll
-      for (int n = 0; n < M; ++n) v[n] = col[2 * n + jodd];
-      regfft::pair_inv<float2, N>(v, jodd);
-      float2 *out = col + (jodd ? M : 0);
-#pragma unroll
-      for (int k = 0; k < M; ++k) out[k] = v[k];
-    }
-    __syncthreads();
-    if (row_lane) {
-      const float2 *row = T + y;
-      float2 v[M];
-#pragma unroll
-      for (int n = 0; n < M; ++n) {
-        const int c = 2 * n + l;
-        const float2 *a = c < ext ? row + c * LD : zslot;
-        v[n] = *a;
-      }
-      regfft::pair_inv<float2, N>(v, odd);
-      const double f = occ[b];
-#pragma unroll
-      for (int k = 0; k < M; ++k) {
-        const double re = v[k].x, im = v[k].y;
-        acc[k] += f * (re * re + im * im);
-      }
-    }
-    __syncthreads();
-  }
-  if (row_lane) {
-    double *out = partial + (((size_t)sub * n3 + z) * N + y) * N + l * M;
-#pragma unroll
-    for (int k = 0; k < M; ++k) out[k] = acc[k];
-  }
-}
-
-// Fused density plane pass on lane quads (FP64 form, N1 = N2 = N a compiled
-// lane-quad size, natural-y plane tables): as the lane-pair form above, with
-// each column and row held by four lanes (quad_inv); 512 threads so that every
-// row has its own quad ((y, q) = (tid / 4, tid % 4), 4 N <= 512).  The inverse
-// leaves lane q with x positions k + (N/4) br(q), k < N/4; the x shift is a
-// unit-modulus phase again.  The per-point sums live in LDS (each lane owns
-// its N/4 entries; in registers they spilled at N = 72).
-constexpr int kDQT = 512;
-
-template <int N>
-__global__ __launch_bounds__(kDQT) __attribute__((amdgpu_waves_per_eu(2))) void k2d_plane_quad(
-    const double2 *__restrict__ sbuf, const double *__restrict__ occ,
-    double *__restrict__ partial, const int *__restrict__ tidx, const double2 *__restrict__ tw_g,
-    int nst, int n3, int ext, int nbk, int bsub) {
-  constexpr int LD = N | 1, Q = N / 4;
-  static_assert(4 * N <= kDQT, "one quad per row");
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  double2 *T = reinterpret_cast<double2 *>(smem_raw);
-  const int tile = ext * LD;
-  const double2 *zslot = T + tile;
-  double2 *twq = T + tile + 1;   // [4][Q]: row q holds W_N^{q k}
-  double *acc = reinterpret_cast<double *>(twq + 4 * Q);   // [N][N] sums of the plane
-  const int z = blockIdx.x % n3;
-  const int sub = blockIdx.x / n3;
-  const int b0 = sub * bsub;
-  const int b1 = min(nbk, b0 + bsub);
-  const int tid = threadIdx.x;
-  const double2 zero = make_double2(0.0, 0.0);
-  const int q = tid & 3;
-  const int bq = ((q & 1) << 1) | (q >> 1);   // two-bit reversal of q
-  const regfft::QuadLane<double> ql(q);
-  const double2 *tw = twq + q * Q;
-  const bool row_lane = tid < 4 * N;
-  const int y = tid >> 2;
-  if (tid == 0) T[tile] = zero;
-  for (int i = tid; i < 4 * Q; i += kDQT) twq[i] = tw_g[((i / Q) * (i % Q)) % N];
-  for (int i = tid; i < N * N; i += kDQT) acc[i] = 0.0;
-  double *mine = acc + y * N + Q * bq;   // this lane's points (row lanes only)
-  for (int b = b0; b < b1; ++b) {
-    for (int i = tid; i < tile; i += kDQT) T[i] = zero;
-    __syncthreads();
-    const double2 *plane = sbuf + ((size_t)b * n3 + z) * nst;
-    for (int s = tid; s < nst; s += kDQT) T[tidx[s]] = plane[s];
-    __syncthreads();
-    for (int j = tid; j < 4 * ext; j += kDQT) {
-      double2 *col = T + (j >> 2) * LD;
-      double2 v[Q];
-#pragma unroll
-      for (int n = 0; n < Q; ++n) v[n] = col[4 * n + q];
-      regfft::quad_inv<double2, N>(v, tw, ql);
-      double2 *out = col + Q * bq;
-#pragma unroll
-      for (int k = 0; k < Q; ++k) out[k] = v[k];
-    }
-    __syncthreads();
-    if (row_lane) {
-      const double2 *row = T + y;
-      double2 v[Q];
-#pragma unroll
-      for (int n = 0; n < Q; ++n) {
-        const int c = 4 * n + q;
-        const double2 *a = c < ext ? row + c * LD : zslot;
-        v[n] = *a;
-      }
-      regfft::quad_inv<double2, N>(v, tw, ql);
-      const double f = occ[b];
-#pragma unroll
-      for (int k = 0; k < Q; ++k) mine[k] += f * (v[k].x * v[k].x + v[k].y * v[k].y);
-    }
-    __syncthreads();
-  }
-  double *out = partial + ((size_t)sub * n3 + z) * N * N;
-  for (int i = tid; i < N * N; i += kDQT) out[i] = acc[i];
-}
-
 // rho[i] = (accumulate ? rho[i] : 0) + scale * sum_sub partial[sub][i], sub in order.
 __global__ __launch_bounds__(256) void density_reduce(const double *__restrict__ partial,
                                                       int nsub, long npts, double scale,
@@ -743,19 +594,18 @@ __global__ __launch_bounds__(256) void density_reduce(const double *__restrict__
 }
 
 // ---------------------------------------------------------------- compiled sizes
-// Square boxes of these sizes report plane path 4 (double precision); the lane-quad
-// density pass is compiled for them.
+// Square boxes of these sizes report plane path 4, in double precision
 #define QEH_QUAD_SIZES(X) X(16) X(20) X(24) X(32) X(36) X(40) X(48) X(60) X(64) X(72)
 
-// ... and in single precision (no density pass of their own).
+// ... and in single precision.
 #define QEH_QUAD32_SIZES(X) X(96) X(120) X(128) X(144) X(160)
 
 // Single-precision sizes: square boxes of these report plane path 2, N3 of these
 // stick path 1.
 #define QEH_PAIR_SIZES(X) \
   X(16) X(18) X(20) X(24) X(30) X(32) X(36) X(40) X(48) X(50) X(54) X(60) X(64) X(72) X(80) X(90)
-// ... and for the density kernels, whose per-point sums add registers (N = 90
-// would spill)
+// ... and for the density rows, whose per-point sums add registers (N = 90 would
+// spill)
 #define QEH_DENSITY_PAIR_SIZES(X) \
   X(16) X(18) X(20) X(24) X(30) X(32) X(36) X(40) X(48) X(50) X(54) X(60) X(64) X(72) X(80)
 
@@ -942,7 +792,7 @@ template <typename C> hipError_t density_columns_impl(const qeh_ctx *c, int nbk,
   const unsigned planes = (unsigned)nbk * c->n3;
   allow_lds(k2a_columns_inv<C>, g.lds_col);
   hipLaunchKernelGGL(k2a_columns_inv<C>, dim3(planes * ncg), dim3(kNT), g.lds_col, c->stream,
-                     reinterpret_cast<const C *>(c->d.sbuf), big, c->d.tidx_dit, c->d.colstart,
+                     reinterpret_cast<const C *>(c->d.sbuf), big, c->d.tidx, c->d.colstart,
                      tw + c->tw_off[1], c->dy, c->nst, c->n3, c->ext, c->pg.ldT, g.cg, ncg,
                      g.cg_div, g.cglast_div);
   return hipGetLastError();
@@ -956,31 +806,6 @@ hipError_t density_rows_pair_launch(const qeh_ctx *c, const DensityGeom &dg, int
   hipLaunchKernelGGL(k2d_rows_pair<N>, dim3((unsigned)nsub * c->n3), dim3(kRT), 0, c->stream,
                      reinterpret_cast<const float2 *>(big), occ_d, partial,
                      reinterpret_cast<const float2 *>(zcol), c->n2, c->n3, c->ext, nbk, dg.bsub);
-  return hipGetLastError();
-}
-
-template <int N>
-hipError_t density_plane_pair_launch(const qeh_ctx *c, const DensityGeom &dg, int nbk,
-                                     const double *occ_d, double *partial) {
-  const int nsub = (nbk + dg.bsub - 1) / dg.bsub;
-  const size_t lds = 8 * ((size_t)c->ext * (N | 1) + 1);
-  allow_lds(k2d_plane_pair<N>, lds);
-  hipLaunchKernelGGL(k2d_plane_pair<N>, dim3((unsigned)nsub * c->n3), dim3(kRT), lds, c->stream,
-                     reinterpret_cast<const float2 *>(c->d.sbuf), occ_d, partial, c->d.tidx,
-                     c->nst, c->n3, c->ext, nbk, dg.bsub);
-  return hipGetLastError();
-}
-
-template <int N>
-hipError_t density_plane_quad_launch(const qeh_ctx *c, const DensityGeom &dg, int nbk,
-                                     const double *occ_d, double *partial) {
-  const int nsub = (nbk + dg.bsub - 1) / dg.bsub;
-  const size_t lds = 16 * ((size_t)c->ext * (N | 1) + 1 + N) + 8 * (size_t)N * N;
-  allow_lds(k2d_plane_quad<N>, lds);
-  hipLaunchKernelGGL(k2d_plane_quad<N>, dim3((unsigned)nsub * c->n3), dim3(kDQT), lds, c->stream,
-                     reinterpret_cast<const double2 *>(c->d.sbuf), occ_d, partial, c->d.tidx,
-                     reinterpret_cast<const double2 *>(c->d.tw) + c->tw_off[0], c->nst, c->n3,
-                     c->ext, nbk, dg.bsub);
   return hipGetLastError();
 }
 
@@ -1022,22 +847,29 @@ bool density_geometry(const qeh_ctx *c, DensityGeom *dg) {
   const char *kern = std::getenv("QEH_DENSITY_KERNEL");
   dg->pair = pair_plane_supported(c->prec, n1, n1) && n1 <= 80 && 2 * n2 <= kRT &&
              !(kern && std::strcmp(kern, "generic") == 0);   // N1 = 90 would spill
-  // fused plane pass: lane-pair plane tables (natural y) and a square plane;
-  // in FP64 the lane-quad form on the lane-quad plane tables
+  // fused plane pass where the two-factor plane kernel runs, its density form is
+  // compiled and its LDS fits
   const bool unfused =
       kern && (std::strcmp(kern, "rows") == 0 || std::strcmp(kern, "generic") == 0);
-  dg->fused = dg->pair && c->plane_path == 2 && n1 == n2 &&
-              8 * ((size_t)c->ext * (n2 | 1) + 1) <= (size_t)kLdsMax && !unfused;
-  dg->fused_quad = c->prec == QEH_FP64 && c->plane_path == 4 && n1 == n2 && 4 * n1 <= kDQT &&
-                   quad_plane_supported(c->prec, n1, n2) &&
-                   16 * ((size_t)c->ext * (n2 | 1) + 1 + n1) + 8 * (size_t)n1 * n1 <=
-                       (size_t)kLdsMax &&
-                   !unfused;
-  if (dg->fused_quad) dg->fused = true;
-  // the fused pass runs its bands one after another per workgroup: smaller
-  // subgroups give more workgroups (measured: 8 bands 0.27 ms, 16 bands
-  // 0.30 ms per 128-band density at the 72^3 cell)
-  if (dg->fused) dg->bsub = 8;
+  const size_t lds2 = !c->two.on || unfused         ? 0
+                      : c->prec == QEH_FP64 ? density_two_lds_f64(n1, c->ext)
+                                            : density_two_lds_f32(n1, c->ext);
+  dg->fused = lds2 > 0 && lds2 <= (size_t)kLdsMax;
+  if (dg->fused) {
+    // it runs its bands one after another per workgroup: subgroups of 4 to 16
+    // bands, whichever leaves the emptiest last wave of workgroups least idle
+    // (two resident per CU if LDS allows)
+    const long slots = 256 * (lds2 <= 80 * 1024 ? 2 : 1);
+    long best = 0;
+    for (int bs = 16; bs >= 4; --bs) {
+      const long wgs = (long)((c->block + bs - 1) / bs) * c->n3;
+      const long rounds = (wgs + slots - 1) / slots * bs;
+      if (best == 0 || rounds < best) {
+        best = rounds;
+        dg->bsub = bs;
+      }
+    }
+  }
   dg->rg = std::max(1, std::min(n2, kDensityPPT * kNT / n1));
   if ((size_t)dg->rg * n1 > (size_t)kDensityPPT * kNT) return false;
   dg->ngroups = (n2 + dg->rg - 1) / dg->rg;
@@ -1054,22 +886,8 @@ hipError_t launch_density_columns(const qeh_ctx *c, int nbk, void *big) {
 
 hipError_t launch_density_plane(const qeh_ctx *c, const DensityGeom &dg, int nbk,
                                 const double *occ_d, double *partial) {
-  if (dg.fused_quad) {
-    switch (c->n1) {
-#define QEH_QUAD_CASE(NN) \
-  case NN: return density_plane_quad_launch<NN>(c, dg, nbk, occ_d, partial);
-      QEH_QUAD_SIZES(QEH_QUAD_CASE)
-#undef QEH_QUAD_CASE
-      default: return hipErrorInvalidValue;
-    }
-  }
-  switch (c->n1) {
-#define QEH_PAIR_CASE(NN) \
-  case NN: return density_plane_pair_launch<NN>(c, dg, nbk, occ_d, partial);
-    QEH_DENSITY_PAIR_SIZES(QEH_PAIR_CASE)
-#undef QEH_PAIR_CASE
-    default: return hipErrorInvalidValue;
-  }
+  return c->prec == QEH_FP64 ? launch_density_two_f64(c, nbk, dg.bsub, occ_d, partial)
+                             : launch_density_two_f32(c, nbk, dg.bsub, occ_d, partial);
 }
 
 hipError_t launch_density_rows(const qeh_ctx *c, const DensityGeom &dg, int nbk, const void *big,

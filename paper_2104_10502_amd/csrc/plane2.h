@@ -232,6 +232,184 @@ template <typename C, int N> hipError_t launch(const qeh_ctx *c, int nbk) {
   return c->two.half ? go(&k2_two<C, N, B, NT, true>) : go(&k2_two<C, N, B, NT, false>);
 }
 
+// Charge density: one workgroup = one z plane of one subgroup of bands, the
+// inverse half of the plane pass for one band after another.  The last pass
+// holds each point's f_b |psi_b|^2 sums in registers, in band order: a thread
+// meets the same (row, k) items for every band (NCH chunks of RC rows, unrolled;
+// the y and x shifts are unit-modulus phases of psi).  Bound: as the plane pass.
+// 72^3, FP64, 128 bands: 261 us on lane quads -> 182.  Whole density of 64 bands
+// on lane quads (FP64) or pairs, or separate column and row passes (*) -> this
+// kernel (us):
+//   FP64  45^3 172* -> 66   60^3 131 -> 96   80^3 423* -> 172   120^2 x 48 519* -> 251
+//   FP32  45^3 151* -> 65   60^3  92 -> 80   80^3 184 -> 115    120^2 x 48 328* -> 202
+// Threads: the sums leave no room for more than 512, and in FP64 up to N = 96 two
+// workgroups of 256 beat one of 512 (N = 72: 182 and 203 us).
+constexpr int density_threads(bool f64, int n) {
+  const int t = threads(f64, n), cap = f64 && n <= 96 ? 256 : 512;
+  return t < cap ? t : cap;
+}
+// Row chunks: so few that two workgroups (or, where the columns alone fill half a
+// CU's LDS, one) are resident with the sphere filling half of a line; 0: not
+// compiled (too many registers: more than four chunks, 64 sums a thread, A > 16).
+constexpr int density_chunks(bool f64, int n) {
+  const int b = factor_b(n), a = n / b, cs = f64 ? 16 : 8;
+  const int ext = n / 2 + 1, tile = ext * pitch(n, b) * cs, row = (a - ext / b) * b * cs;
+  const int cap = tile < 72 * 1024 ? 80 * 1024 : 156 * 1024;
+  const int nta = density_threads(f64, n) / a * a;
+  for (int c = 1; c <= 4 && a <= 16; ++c) {
+    const int rc = (n + c - 1) / c;
+    if (tile + (rc | 1) * row <= cap) return c * ((rc * a + nta - 1) / nta) * b <= 64 ? c : 0;
+  }
+  return 0;
+}
+
+template <typename C, int N, int NCH, bool HALF>
+__global__ __launch_bounds__(density_threads(sizeof(C) == 16, N)) void k2d_two(
+    const C *__restrict__ sbuf, const double *__restrict__ occ, double *__restrict__ partial,
+    const int *__restrict__ tidx, const C *__restrict__ tw, int nst, int n3, int ext, int nbk,
+    int bsub) {
+  constexpr int NT = density_threads(sizeof(C) == 16, N);
+  constexpr int B = factor_b(N), A = N / B, BP = pitch_b(B), LD = pitch(N, B);
+  constexpr int AU = HALF ? (A + 1) / 2 : A;
+  constexpr int NTA = NT / A * A;
+  constexpr int RC = (N + NCH - 1) / NCH, ER = RC | 1, IT = (RC * A + NTA - 1) / NTA;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  const int z = blockIdx.x % n3, sub = blockIdx.x / n3;
+  const int tid = threadIdx.x;
+  C *T = reinterpret_cast<C *>(smem_raw);
+  C *E = T + ext * LD;
+  const int k0 = ext / B;
+  const int myk = tid % A;
+  C w[B];   // W^{b k} = exp(-2 pi i b k / N)
+#pragma unroll
+  for (int b = 1; b < B; ++b) w[b] = tw[b * myk];
+  double acc[NCH][IT][B];
+#pragma unroll
+  for (int i = 0; i < NCH * IT * B; ++i) acc[i / (IT * B)][i / B % IT][i % B] = 0.0;
+
+  for (int band = sub * bsub; band < min(nbk, (sub + 1) * bsub); ++band) {
+    const C *plane = sbuf + ((size_t)band * n3 + z) * nst;
+    for (int i = tid; i < ext * (AU * B); i += NT) {
+      const int c = i / (AU * B), p = i - c * (AU * B);
+      T[c * LD + p / B * BP + p % B] = cmk<C>(0, 0);
+    }
+    __syncthreads();
+    for (int s = tid; s < nst; s += NT) T[tidx[s]] = plane[s];
+    __syncthreads();
+    for (int t = tid; t < ext * B; t += NT) {
+      const int c = t / B, b = t - c * B;
+      C *col = T + c * LD + b;
+      C v[A];
+#pragma unroll
+      for (int a = 0; a < A; ++a) v[a] = a < AU ? col[a * BP] : cmk<C>(0, 0);
+      regfft::Fft<C, A, true>::run(v);
+#pragma unroll
+      for (int k = 0; k < A; ++k) col[k * BP] = v[k];
+    }
+    __syncthreads();
+    if (tid < NTA)
+      for (int t = tid; t < ext * A; t += NTA) {
+        C *col = T + t / A * LD + myk * BP;
+        C v[B];
+#pragma unroll
+        for (int b = 0; b < B; ++b) v[b] = b ? cmulc(col[b], w[b]) : col[0];
+        regfft::Fft<C, B, true>::run(v);
+#pragma unroll
+        for (int q = 0; q < B; ++q) col[q] = v[q];
+      }
+    __syncthreads();
+    const double f = occ[band];
+#pragma unroll
+    for (int ch = 0; ch < NCH; ++ch) {
+      const int s0 = ch * RC, nr = min(RC, N - s0);
+      for (int t = tid; t < nr * B; t += NT) {
+        const int r = t / B, b = t - r * B;
+        const int s = s0 + r;
+        C *row = T + b * LD + s / B * BP + s % B;
+        C *er = E + b * ER + r;
+        C v[A];
+#pragma unroll
+        for (int a = 0; a < A; ++a)
+          v[a] = a < AU && a * B + b < ext ? row[a * (B * LD)] : cmk<C>(0, 0);
+        regfft::Fft<C, A, true>::run(v);
+#pragma unroll
+        for (int k = 0; k < A; ++k) {
+          C *p = k < k0 ? row + k * (B * LD) : er + (k - k0) * (B * ER);
+          *p = v[k];
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int it = 0; it < IT; ++it) {
+        const int t = tid + it * NTA;
+        if (tid < NTA && t < nr * A) {
+          const int r = t / A, s = s0 + r;
+          const int st = myk < k0 ? LD : ER;
+          const C *p =
+              myk < k0 ? T + myk * (B * LD) + s / B * BP + s % B : E + (myk - k0) * (B * ER) + r;
+          C v[B];
+#pragma unroll
+          for (int b = 0; b < B; ++b) v[b] = b ? cmulc(p[b * st], w[b]) : p[0];
+          regfft::Fft<C, B, true>::run(v);
+#pragma unroll
+          for (int q = 0; q < B; ++q) {
+            const double re = v[q].x, im = v[q].y;
+            acc[ch][it][q] += f * (re * re + im * im);
+          }
+        }
+      }
+      __syncthreads();
+    }
+  }
+  double *out = partial + ((size_t)sub * n3 + z) * N * N;
+#pragma unroll
+  for (int ch = 0; ch < NCH; ++ch)
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const int t = tid + it * NTA, s = ch * RC + t / A;
+      if (tid < NTA && t < min(RC, N - ch * RC) * A) {
+        double *row = out + (size_t)(s / B + A * (s % B)) * N + myk;
+#pragma unroll
+        for (int q = 0; q < B; ++q) row[A * q] = acc[ch][it][q];
+      }
+    }
+}
+
+// LDS of the density pass, 0 where it is not compiled.
+template <typename C, int N> size_t density_lds(int ext) {
+  constexpr int NCH = density_chunks(sizeof(C) == 16, N);
+  if constexpr (NCH == 0) {
+    return 0;
+  } else {
+    constexpr int B = factor_b(N), A = N / B, RC = (N + NCH - 1) / NCH;
+    return sizeof(C) * ((size_t)ext * pitch(N, B) + (size_t)(A - ext / B) * B * (RC | 1));
+  }
+}
+
+template <typename C, int N>
+hipError_t launch_density(const qeh_ctx *c, int nbk, int bsub, const double *occ,
+                          double *partial) {
+  constexpr int NCH = density_chunks(sizeof(C) == 16, N);
+  if constexpr (NCH == 0) {
+    return hipErrorInvalidValue;
+  } else {
+    const size_t lds = density_lds<C, N>(c->ext);
+    const int nsub = (nbk + bsub - 1) / bsub;
+    auto go = [&](auto kern) {
+      if (lds > 64 * 1024)
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      hipLaunchKernelGGL(kern, dim3((unsigned)nsub * c->n3),
+                         dim3(density_threads(sizeof(C) == 16, N)), lds, c->stream,
+                         reinterpret_cast<const C *>(c->d.sbuf), occ, partial, c->d.tidx2,
+                         reinterpret_cast<const C *>(c->d.tw) + c->tw_off[0], c->nst, c->n3, c->ext,
+                         nbk, bsub);
+      return hipGetLastError();
+    };
+    return c->two.half ? go(&k2d_two<C, N, NCH, true>) : go(&k2d_two<C, N, NCH, false>);
+  }
+}
+
 // Sizes compiled: products of 2, 3, 5, 7 up to 192 with both factors <= 16, and 125.
 #define QEH_TWO_SIZES(X)                                                                       \
   X(12) X(14) X(15) X(16) X(18) X(20) X(21) X(24) X(25) X(27) X(28) X(30) X(32) X(35) X(36)    \

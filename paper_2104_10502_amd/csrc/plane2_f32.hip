@@ -55,4 +55,25 @@ bool two_geometry(int prec, int n1, int n2, int ext, int exty, TwoGeom *g) {
   return false;
 }
 
+hipError_t launch_density_two_f32(const qeh_ctx *c, int nbk, int bsub, const double *occ,
+                                  double *partial) {
+  switch (c->n1) {
+#define QEH_TWO_CASE(NN) \
+  case NN: return plane2::launch_density<float2, NN>(c, nbk, bsub, occ, partial);
+    QEH_TWO_SIZES(QEH_TWO_CASE)
+#undef QEH_TWO_CASE
+    default: return hipErrorInvalidValue;
+  }
+}
+
+size_t density_two_lds_f32(int n, int ext) {
+  switch (n) {
+#define QEH_TWO_CASE(NN) \
+  case NN: return plane2::density_lds<float2, NN>(ext);
+    QEH_TWO_SIZES(QEH_TWO_CASE)
+#undef QEH_TWO_CASE
+    default: return 0;
+  }
+}
+
 }  // namespace qeh

@@ -84,10 +84,8 @@ struct DevMaps {
   int *stick_off;    // [nst+1] first G of each stick
   int *gmap;         // [npw] s*ldz + digit-reversed z position (two-factor K1 / K3:
                      // s * their pitch + slot)
-  int *tidx;         // [nst] plane-tile index c*ldT + pos_y(k mod N2); the lane-pair
-                     // and lane-quad density passes take natural y (pos_y = identity)
-  int *tidx2;        // [nst] the same for the two-factor plane kernel (y shifted to k - kmin)
-  int *tidx_dit;     // [nst] the same with pos_y the y-DIT input position (always)
+  int *tidx;         // [nst] plane-tile index c*ldT + y-DIT input position of k mod N2
+  int *tidx2;        // [nst] c*ldT + slot of k - kmin, for the two-factor plane kernel
   int *xin;          // [N1] column c whose h sits at x-DIT input position p, or -1
   double *kin;       // [npw] |k+G|^2
   double *hdiag;     // [npw] diag(H)
@@ -120,8 +118,8 @@ struct qeh_ctx {
   int has_q = 0;        // 1: overlap q blocks present (S != 1)
   int n1 = 0, n2 = 0, n3 = 0, ext = 0, hmin = 0;
   int block = 0, prec = 0;
-  int plane_path = 0;   // 0 one kernel, 1 split through HBM; 2, 4: one kernel, natural-order
-                        // y tables for the lane-pair / lane-quad density passes
+  int plane_path = 0;   // as reported: 0 one kernel, 1 split through HBM; 2, 4: one kernel,
+                        // boxes of the lane-pair / lane-quad sizes
   int stick_path = 0;   // as reported: 1 for single-precision N3 of a lane-pair size
   int nsplit = 1, kchunk = 0;
   int wide = 0;         // 1: wide single-precision tiles for the projector products
@@ -183,8 +181,7 @@ hipError_t launch_k3_two_f64(const qeh_ctx *c, int nbk, const double2 *psi, int 
 bool stick_two_geometry(int prec, int n3, int lmin, int lmax, StickTwoGeom *g);
 size_t plane_lds_bytes(int prec, int ext, int n1, int n2, const PlaneGeom &g);
 size_t stick_lds_bytes(int prec, int n3, const StickGeom &g);
-// Square boxes whose density passes are the lane-pair (single precision) or
-// lane-quad (FP64) kernels.
+// Square boxes that report plane path 2 or 4.
 bool pair_plane_supported(int prec, int n1, int n2);
 bool quad_plane_supported(int prec, int n1, int n2);
 
@@ -198,9 +195,7 @@ hipError_t launch_k2_two_f64(const qeh_ctx *c, int nbk);
 struct DensityGeom {
   int rg, ngroups, bsub;
   bool pair;    // lane-pair rows kernel (partial planes in the same layout)
-  bool fused;   // fused plane kernel (lane pairs, or lane quads in FP64): no column
-                // pass through HBM
-  bool fused_quad;   // the FP64 lane-quad form of the fused kernel
+  bool fused;   // the two-factor plane kernel: no column pass through HBM
   size_t lds;
   FastDiv rg_div, rglast_div;
 };
@@ -215,6 +210,13 @@ hipError_t launch_density_rows(const qeh_ctx *c, const DensityGeom &dg, int nbk,
 // Fused form (dg.fused): sticks -> columns -> rows -> partial planes in one pass.
 hipError_t launch_density_plane(const qeh_ctx *c, const DensityGeom &dg, int nbk,
                                 const double *occ_d, double *partial);
+hipError_t launch_density_two_f32(const qeh_ctx *c, int nbk, int bsub, const double *occ,
+                                  double *partial);
+hipError_t launch_density_two_f64(const qeh_ctx *c, int nbk, int bsub, const double *occ,
+                                  double *partial);
+// LDS of the fused pass, 0 where it is not compiled.
+size_t density_two_lds_f32(int n, int ext);
+size_t density_two_lds_f64(int n, int ext);
 hipError_t launch_density_reduce(const double *partial, int nsub, long npts, double scale,
                                  double *rho, int accumulate, hipStream_t s);
 
