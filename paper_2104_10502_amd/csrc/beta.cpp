@@ -7,6 +7,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <string>
 #include <vector>
 
@@ -43,18 +44,30 @@ long total_channels(const qeh_projgen *p) {
   return n;
 }
 
-// q = k + G for every G, SoA [3][npw]
-std::vector<double> qvectors(const qeh_cell *c) {
+// The largest |k+G|^2.  In a run of equal (h, k) it is convex in l, so only the
+// run's least and greatest l are evaluated.
+double largest_q2(const qeh_cell *c) {
   double b[9];
   recip_rows(c->lattice, b);
+  double best = 0.0;
+  auto at = [&](int h, int k, int l) {
+    double q[3];
+    for (int i = 0; i < 3; ++i) q[i] = c->kpt[i] + h * b[i] + k * b[3 + i] + l * b[6 + i];
+    best = std::max(best, q[0] * q[0] + q[1] * q[1] + q[2] * q[2]);
+  };
   const size_t npw = c->npw;
-  std::vector<double> q(3 * npw);
-  for (size_t g = 0; g < npw; ++g) {
-    const int *m = c->miller + 3 * g;
-    for (int i = 0; i < 3; ++i)
-      q[i * npw + g] = c->kpt[i] + m[0] * b[i] + m[1] * b[3 + i] + m[2] * b[6 + i];
+  const int *m = c->miller;
+  for (size_t g = 0; g < npw;) {
+    const int h = m[3 * g], k = m[3 * g + 1];
+    int lo = m[3 * g + 2], hi = lo;
+    for (++g; g < npw && m[3 * g] == h && m[3 * g + 1] == k; ++g) {
+      lo = std::min(lo, m[3 * g + 2]);
+      hi = std::max(hi, m[3 * g + 2]);
+    }
+    at(h, k, lo);
+    at(h, k, hi);
   }
-  return q;
+  return best;
 }
 
 }  // namespace
@@ -121,13 +134,7 @@ qeh_status projgen_validate(const qeh_cell *c) {
       return QEH_ERR_NUMERIC;
     }
   // every |k+G| inside the table's interpolation range
-  const std::vector<double> q = qvectors(c);
-  const size_t npw = c->npw;
-  double qmax = 0.0;
-  for (size_t g = 0; g < npw; ++g) {
-    const double x = q[g], y = q[npw + g], z = q[2 * npw + g];
-    qmax = std::max(qmax, std::sqrt(x * x + y * y + z * z));
-  }
+  const double qmax = std::sqrt(largest_q2(c));
   if (qmax > (p->nq - 3) * p->dq)
     return bad("projgen table ends at " + std::to_string((p->nq - 3) * p->dq) +
                " bohr^-1 but the sphere reaches |k+G| = " + std::to_string(qmax));
@@ -139,11 +146,14 @@ qeh_status projgen_run(const qeh_cell *c, bool f64, void *out, long ldb, char *w
   const qeh_projgen *p = c->projgen;
   const ProjgenLayout L = projgen_layout(c);
   const long nch = total_channels(p);
-  const std::vector<double> q = qvectors(c);
-  std::vector<int> chan0(p->nsp + 1, 0);
+  // everything but the Miller list in one piece: one upload
+  std::vector<char> stage(L.total - L.off_atom);
+  auto in_stage = [&](size_t off) { return static_cast<void *>(stage.data() + (off - L.off_atom)); };
+  int *chan0 = static_cast<int *>(in_stage(L.off_chan0));
+  chan0[0] = 0;
   for (int sp = 0; sp < p->nsp; ++sp) chan0[sp + 1] = chan0[sp] + p->nchan[sp];
-  std::vector<int4> atoms(c->nat);
   {
+    int4 *atoms = static_cast<int4 *>(in_stage(L.off_atom));
     int row = 0, doff = 0;
     for (int a = 0; a < c->nat; ++a) {
       const int n = c->nproj[a];
@@ -152,27 +162,30 @@ qeh_status projgen_run(const qeh_cell *c, bool f64, void *out, long ldb, char *w
       doff += n * n;
     }
   }
+  std::memcpy(in_stage(L.off_tau), p->tau, 24 * (size_t)c->nat);
+  if (nch > 0) {
+    std::memcpy(in_stage(L.off_lchan), p->lchan, 4 * (size_t)nch);
+    std::memcpy(in_stage(L.off_tab), p->tab, 8 * (size_t)nch * p->nq);
+  }
   const double *A = c->lattice;
   const double omega =
       std::fabs(A[0] * (A[4] * A[8] - A[5] * A[7]) - A[1] * (A[3] * A[8] - A[5] * A[6]) +
                 A[2] * (A[3] * A[7] - A[4] * A[6]));
   const double pref = 4.0 * M_PI / std::sqrt(omega);
-  hipError_t e = hipSuccess;
-  auto up = [&](size_t off, const void *src, size_t bytes) {
-    if (e == hipSuccess && bytes)
-      e = hipMemcpyAsync(work + off, src, bytes, hipMemcpyHostToDevice, s);
-  };
-  up(L.off_q, q.data(), 8 * q.size());
-  up(L.off_atom, atoms.data(), sizeof(int4) * atoms.size());
-  up(L.off_tau, p->tau, 24 * (size_t)c->nat);
-  up(L.off_chan0, chan0.data(), 4 * chan0.size());
-  if (nch > 0) {
-    up(L.off_lchan, p->lchan, 4 * (size_t)nch);
-    up(L.off_tab, p->tab, 8 * (size_t)nch * p->nq);
+  double rec[9];
+  recip_rows(A, rec);
+  ProjgenFrame fr;
+  for (int i = 0; i < 3; ++i) {
+    fr.k[i] = c->kpt[i];
+    for (int j = 0; j < 3; ++j) fr.b[j][i] = rec[3 * j + i];
   }
+  hipError_t e = hipMemcpyAsync(work + L.off_q, c->miller, 12 * (size_t)c->npw,
+                                hipMemcpyHostToDevice, s);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(work + L.off_atom, stage.data(), stage.size(), hipMemcpyHostToDevice, s);
   const int4 *atoms_d = reinterpret_cast<const int4 *>(work + L.off_atom);
   if (e == hipSuccess)
-    e = launch_beta_gen(f64, reinterpret_cast<const double *>(work + L.off_q), c->npw, c->nat,
+    e = launch_beta_gen(f64, reinterpret_cast<const int *>(work + L.off_q), fr, c->npw, c->nat,
                         atoms_d, reinterpret_cast<const double *>(work + L.off_tau),
                         reinterpret_cast<const int *>(work + L.off_chan0),
                         reinterpret_cast<const int *>(work + L.off_lchan),
@@ -180,7 +193,7 @@ qeh_status projgen_run(const qeh_cell *c, bool f64, void *out, long ldb, char *w
                         out, ldb, s);
   if (e == hipSuccess && hdiag_dev)
     e = launch_nl_diag(f64, out, ldb, c->npw, c->nat, atoms_d, dmat_dev, hdiag_dev, s);
-  // the staging vectors are host locals: wait before they go
+  // the staging vector is a host local: wait before it goes
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return hip_fail(e, "projector generation");
   return QEH_OK;

@@ -221,9 +221,10 @@ hipError_t launch_density_reduce(const double *partial, int nsub, long npts, dou
                                  double *rho, int accumulate, hipStream_t s);
 
 // ---- projectors built on the device (beta.cpp, beta_kernels.hip) -----------
-// Workspace of the generator: k+G vectors [3][npw] (SoA), per-atom int4
-// {species, first row, projectors, D offset}, positions [nat][3], channel
-// offsets per species [nsp+1], l per channel, tables [channels][nq].
+// Workspace of the generator: the Miller list [npw][3] (in room for twice as
+// much), per-atom int4 {species, first row, projectors, D offset}, positions
+// [nat][3], channel offsets per species [nsp+1], l per channel, tables
+// [channels][nq].
 struct ProjgenLayout {
   size_t off_q, off_atom, off_tau, off_chan0, off_lchan, off_tab, total;
 };
@@ -236,10 +237,14 @@ qeh_status projgen_validate(const qeh_cell *c);
 // part of diag(H) (D blocks from dmat_dev); returns after the stream drained.
 qeh_status projgen_run(const qeh_cell *c, bool f64, void *out, long ldb, char *work,
                        hipStream_t s, const double2 *dmat_dev, double *hdiag_dev);
-hipError_t launch_beta_gen(bool f64, const double *q, int npw, int nat, const int4 *atoms,
-                           const double *tau, const int *chan0, const int *lchan,
-                           const double *tab, int nq, double dq, double pref, void *beta,
-                           long ldb, hipStream_t s);
+// k and the reciprocal rows b[j] of the kernel's q = k + h b[0] + k b[1] + l b[2].
+struct ProjgenFrame {
+  double k[3], b[3][3];
+};
+hipError_t launch_beta_gen(bool f64, const int *miller, const ProjgenFrame &fr, int npw, int nat,
+                           const int4 *atoms, const double *tau, const int *chan0,
+                           const int *lchan, const double *tab, int nq, double dq, double pref,
+                           void *beta, long ldb, hipStream_t s);
 hipError_t launch_nl_diag(bool f64, const void *beta, long ldb, int npw, int nat,
                           const int4 *atoms, const double2 *dmat, double *hdiag,
                           hipStream_t s);
