@@ -21,6 +21,7 @@
 #include "cplx.h"
 #include "fft_radix.h"
 #include "fft_reg.h"
+#include "plane2.h"
 #include "qeh_internal.h"
 
 namespace qeh {
@@ -857,9 +858,11 @@ bool density_geometry(const qeh_ctx *c, DensityGeom *dg) {
   dg->fused = lds2 > 0 && lds2 <= (size_t)kLdsMax;
   if (dg->fused) {
     // it runs its bands one after another per workgroup: subgroups of 4 to 16
-    // bands, whichever leaves the emptiest last wave of workgroups least idle
-    // (two resident per CU if LDS allows)
-    const long slots = 256 * (lds2 <= 80 * 1024 ? 2 : 1);
+    // bands, whichever leaves the last round of workgroups least idle (as many
+    // resident per CU as its LDS and 16 waves allow; whole density of 200 bands on
+    // 36^3, mixed: 81 us with two assumed, 69; of 128 on 72^3 167 and 152)
+    const int wg_waves = plane2::density_threads(c->prec == QEH_FP64, n1) / 64;
+    const long slots = 256 * std::max<long>(1, std::min<long>(kLdsMax / (long)lds2, 16 / wg_waves));
     long best = 0;
     for (int bs = 16; bs >= 4; --bs) {
       const long wgs = (long)((c->block + bs - 1) / bs) * c->n3;
