@@ -489,10 +489,12 @@ qeh_status qeh_server_destroy(qeh_server *srv);
 
 /* Shape facts of a context: [npw, nst, nkb, N1, N2, N3, x-extent, block,
  * precision, plane path (0 one kernel, 1 split through HBM; 2 and 4: one
- * kernel, on a box whose density runs the lane-pair / lane-quad passes),
- * stick path (1 in the mixed form with N3 = 16, 18, 20, 24, 30, 32, 36, 40, 48,
- * 50, 54, 60, 64, 72, 80 or 90, else 0), projector
- * tiles (0 the 64-row MFMA tiles, 1 the wide single-precision tiles:
+ * kernel, on square boxes of some sizes: 2 in the mixed form with N1 = N2 = 16,
+ * 18, 20, 24, 30, 32, 36, 40, 48, 50, 54, 60, 64, 72, 80 or 90; 4 in FP64 with 16,
+ * 20, 24, 32, 36, 40, 48, 60, 64 or 72 and in the mixed form with 96, 120, 128,
+ * 144 or 160),
+ * stick path (1 in the mixed form with N3 one of plane path 2's sizes, else 0),
+ * projector tiles (0 the 64-row MFMA tiles, 1 the wide single-precision tiles:
  * QEH_MIXED with >= 2048 projectors and a block of >= 128 bands)].  out has
  * room for n values (up to 12).
  * The plane pass takes the two-factor kernel on square planes (N1 = N2) of a
