@@ -7,17 +7,18 @@
 // its registers.
 //
 // W waves; wave w holds columns w + W c (c < KC), lane l rows l (and l + 64):
-// 4 waves of 8 columns for orders up to 32, of 16 up to 64, 8 waves of 16
-// columns with two rows a lane up to 128 (256 KB of the CU's 512 KB register
-// file).  A step moves vectors only through LDS.  What bounds them is the
+// 4 waves of 8, 12 or 16 columns for orders up to 32, 48 and 64, 8 waves of 10 to
+// 16 columns with two rows a lane up to 80, 96, 112 and 128 (256 KB of the CU's
+// 512 KB register file).  A step moves vectors only through LDS.  What bounds them is the
 // issue of a step's instructions and its chain, so: few waves (what each does
 // for itself is paid fewer times), no branches but four stages of the step loop
 // that leave out the columns (and rows) already done, and the wave that owns the
 // next column brings that one up to date first and works out its pivot or
 // reflector while the others still update theirs.
-// Tridiagonalisation at orders around 120: 294 us (43 launches of a step each and
-// an LDS-resident last 64 took 433); at 64: 101 us (188).  Cholesky around 120:
-// 85 us (123 in seven launches); at 64: 41 us.
+// Tridiagonalisation, order 48 71 us, 64 102, 80 182, 96 223, 112 279, 128 325 (at
+// about 110, 43 launches of a step each and an LDS-resident last 64 took 433, at
+// 64 the latter 188; 16 columns a wave whatever the order: 48 84, 80 255, 96 283).
+// Cholesky: 29, 41, 58, 71, 88, 98 us (at about 110, seven launches 123).
 #include "eigh_vec.h"
 
 namespace qeh {
@@ -217,7 +218,7 @@ template <int RS, int W, int KC> struct Tridiag {
   template <int C0> __device__ __forceinline__ bool stage() {
     constexpr int R0 = C0 * W >= 64 ? RS - 1 : 0;
     constexpr int NC = KC - C0 > 8 ? 16 : KC - C0 > 4 ? 8 : 4;   // columns in the lane sums
-    constexpr int CB = KC - NC;
+    constexpr int CB = KC - NC;   // (below 0: zeros fill up the first values)
     const int end = min(m - 1, (C0 + kStage) * W);
     for (int k = C0 * W; k < end; ++k) {
       __syncthreads();
@@ -242,7 +243,7 @@ template <int RS, int W, int KC> struct Tridiag {
         }
         const double ysum = LaneSums<2 * NC, 32>::of(x, lane);
         constexpr int LV = 32 / NC;   // lanes per value
-        if ((lane & (LV - 1)) == 0)
+        if ((lane & (LV - 1)) == 0 && (CB >= 0 || CB + lane / (2 * LV) >= 0))
           reinterpret_cast<double *>(ys)[2 * (w + W * (CB + lane / (2 * LV))) +
                                          ((lane / LV) & 1)] = ysum;
         __syncthreads();
@@ -325,8 +326,12 @@ hipError_t launch_chol_reg(double2 *S, long ld, int n, int *info, hipStream_t s)
     return hipGetLastError();
   };
   return n <= 32   ? go(chol_reg_kernel<1, 4, 8>, 4)
+         : n <= 48 ? go(chol_reg_kernel<1, 4, 12>, 4)
          : n <= 64 ? go(chol_reg_kernel<1, 4, 16>, 4)
-                   : go(chol_reg_kernel<2, 8, 16>, 8);
+         : n <= 80 ? go(chol_reg_kernel<2, 8, 10>, 8)
+         : n <= 96 ? go(chol_reg_kernel<2, 8, 12>, 8)
+         : n <= 112 ? go(chol_reg_kernel<2, 8, 14>, 8)
+                     : go(chol_reg_kernel<2, 8, 16>, 8);
 }
 
 hipError_t launch_tridiag_reg(double2 *A, long lda, int m, double *d, double *e, double2 *tau,
@@ -337,8 +342,12 @@ hipError_t launch_tridiag_reg(double2 *A, long lda, int m, double *d, double *e,
     return hipGetLastError();
   };
   return m <= 32   ? go(tridiag_reg_kernel<1, 4, 8>, 4)
+         : m <= 48 ? go(tridiag_reg_kernel<1, 4, 12>, 4)
          : m <= 64 ? go(tridiag_reg_kernel<1, 4, 16>, 4)
-                   : go(tridiag_reg_kernel<2, 8, 16>, 8);
+         : m <= 80 ? go(tridiag_reg_kernel<2, 8, 10>, 8)
+         : m <= 96 ? go(tridiag_reg_kernel<2, 8, 12>, 8)
+         : m <= 112 ? go(tridiag_reg_kernel<2, 8, 14>, 8)
+                     : go(tridiag_reg_kernel<2, 8, 16>, 8);
 }
 
 hipError_t launch_trsm_small(int mode, const double2 *T, long ldt, int n, const double2 *B,

@@ -1,6 +1,6 @@
 """The dense solver of the Rayleigh-Ritz step at the edges of its register,
-LDS and workgroup shares: orders around 32, 64, 128 and 256 (where the kernels
-change), one eigenpair and all of them, multiplets longer than a workgroup's
+LDS and workgroup shares: orders around 32, 48, 64, 80, 96, 112, 128 and 256 (where
+the kernels change), one eigenpair and all of them, multiplets longer than a workgroup's
 share of 16, off-diagonal elements whose squares underflow, and a matrix that
 stops being positive definite at a given pivot.
 
@@ -17,7 +17,8 @@ import scipy.linalg as sla
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
-ORDERS = [1, 2, 3, 15, 16, 17, 31, 32, 33, 63, 64, 65, 66, 127, 128, 129, 130, 255, 256, 257]
+ORDERS = [1, 2, 3, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 64, 65, 66, 79, 80, 81, 96, 97, 112, 113,
+          127, 128, 129, 130, 255, 256, 257]
 
 
 def _random(rng, n):
