@@ -7,22 +7,24 @@ namespace qeh {
 namespace {
 
 // ---------------------------------------------------------------- tridiagonal eigenpairs
-// Number of eigenvalues of the block [s, t) of T (split e) below x.
-// Sign changes of the principal minors p_i of T_b - x I, by the recurrence
+// Number of eigenvalues below x of rows [s, t) of T, scaled to 1/2 <= ||T|| < 1:
+// of one block of the split T, or of all of T with its blocks joined by
+// kSplitE ||T||.
+// Sign changes of the principal minors p_i of T - x I, by the recurrence
 // p_i = (d_i - x) p_{i-1} - e_{i-1}^2 p_{i-2}: one fused multiply-add a row on
 // the dependent chain, where the quotients p_i / p_{i-1} take a reciprocal
-// estimate and two Newton steps.  x and T are scaled by sc, a power of two of the
-// size of 1 / ||T||, so that a chunk of kSU rows grows the pair by at most 4^kSU,
-// and, e^2 being at least eps^2 / 4, never takes both to zero; after each chunk
-// the pair is scaled by a power of two.  A zero p_i counts as positive: with p_{i+1} of the sign
+// estimate and two Newton steps.  T being scaled, a chunk of kSU rows grows the
+// pair by at most 4^kSU, and, no e^2 being below (kSplitE / 2)^2, never takes both
+// to zero; after each chunk the pair is scaled by a power of two.  (Over an e^2
+// of zero it could: with d_i = x every later p would be a zero of either sign.)
+// A zero p_i counts as positive: with p_{i+1} of the sign
 // opposite to p_{i-1} the pair of rows has one change either way.  The
 // operands (LDS) are read a chunk ahead.
 constexpr int kSU = 8;
-__device__ __forceinline__ int sturm_count(const double *d, const double *e2, int s, int t, double x,
-                                           double sc) {
-  const double xs = x * sc;
-  double p1 = fma(d[s], sc, -xs), p2 = 1.0;
-  const double sc2 = sc * sc;
+constexpr double kSplitE = 0.125 * kEps;
+__device__ __forceinline__ int sturm_count(const double *d, const double *e2, int s, int t,
+                                           double x) {
+  double p1 = d[s] - x, p2 = 1.0;
   int c = __double2hiint(p1) < 0 ? 1 : 0;
   int i = s + 1;
   double dn[kSU], en[kSU];
@@ -37,8 +39,8 @@ __device__ __forceinline__ int sturm_count(const double *d, const double *e2, in
     double dc[kSU], ec[kSU];
 #pragma unroll
     for (int u = 0; u < kSU; ++u) {
-      dc[u] = fma(dn[u], sc, -xs);
-      ec[u] = en[u] * sc2;
+      dc[u] = dn[u] - x;
+      ec[u] = en[u];
     }
     if (i + 2 * kSU <= t) {
 #pragma unroll
@@ -59,7 +61,7 @@ __device__ __forceinline__ int sturm_count(const double *d, const double *e2, in
     p2 = __builtin_amdgcn_ldexp(p2, ex);
   }
   for (; i < t; ++i) {
-    const double p = fma(fma(d[i], sc, -xs), p1, -(e2[i - 1] * sc2 * p2));
+    const double p = fma(d[i] - x, p1, -(e2[i - 1] * p2));
     c += (unsigned)(__double2hiint(p) ^ __double2hiint(p1)) >> 31;
     p2 = p1;
     p1 = p;
@@ -171,19 +173,26 @@ __global__ __launch_bounds__(NT) void trieig_kernel(const double *tri, int n, in
   }
   md = block_max<NW>(md, red);
   me = block_max<NW>(me, red);
-  const double tnorm = md + 2.0 * me;
+  double tnorm = md + 2.0 * me;
   if (!isfinite(tnorm) || nb < 1 || nb > n) {
     if (PH == 0 && blockIdx.x == 0 && tid == 0) *info = 1;
     return;
   }
-  // a power of two of the size of 1 / ||T|| (exact scaling of the Sturm counts)
-  const double sc = __builtin_amdgcn_ldexp(1.0, -__builtin_amdgcn_frexp_exp(tnorm));
-  // split where |e| is negligible
+  // T scaled by a power of two to 1/2 <= ||T|| < 1 (exact; the eigenvalues are
+  // scaled back where they are written): the squares neither overflow nor lose
+  // their digits
+  const int tex = __builtin_amdgcn_frexp_exp(tnorm);
+  tnorm = tnorm > 0.0 ? __builtin_amdgcn_ldexp(tnorm, -tex) : 1.0;
+  // split where |e| is negligible; the squares there, which only the counts over
+  // all of T read, move its eigenvalues by less than kEps ||T||
   double e2max = 0.0;
   for (int i = tid; i < n; i += NT) {
-    if (fabs(se[i]) <= kEps * tnorm) se[i] = 0.0;
-    se2[i] = se[i] * se[i];
-    e2max = fmax(e2max, se2[i]);
+    sd[i] = __builtin_amdgcn_ldexp(sd[i], -tex);
+    const double e = __builtin_amdgcn_ldexp(se[i], -tex);
+    const bool split = fabs(e) <= kEps * tnorm;
+    se[i] = split ? 0.0 : e;
+    se2[i] = split ? kSplitE * tnorm * (kSplitE * tnorm) : e * e;
+    e2max = fmax(e2max, se[i] * se[i]);
   }
   e2max = block_max<NW>(e2max, red);
   const double pivmin = kTiny * fmax(1.0, e2max);
@@ -234,7 +243,7 @@ __global__ __launch_bounds__(NT) void trieig_kernel(const double *tri, int n, in
       const double a = sh_d[0], b = sh_d[1];
       if (b - a <= 2.0 * kEps * tnorm || cup == nb) break;   // uniform
       const double x = a + (b - a) * (double)(tid + 1) / (double)(NT + 1);
-      const int c = sturm_count(sd, se2, 0, n, x, sc);
+      const int c = sturm_count(sd, se2, 0, n, x);
       if (tid == 0) sh_i[2] = NT;
       __syncthreads();
       if (c > nb - 1) atomicMin(&sh_i[2], tid);   // first point above: order-free minimum
@@ -255,7 +264,7 @@ __global__ __launch_bounds__(NT) void trieig_kernel(const double *tri, int n, in
   const double xcut = PH == 0 ? sh_d[1] + 4.0 * kEps * tnorm + pivmin : *xcut_g;
   if (PH == 0 && blockIdx.x == 0 && tid == 0) *xcut_g = xcut;
   // eigenvalues of each block below the cut -> tasks
-  for (int b = tid; b < nblk; b += NT) bof[b] = sturm_count(sd, se2, bst[b], bst[b + 1], xcut, sc);
+  for (int b = tid; b < nblk; b += NT) bof[b] = sturm_count(sd, se2, bst[b], bst[b + 1], xcut);
   __syncthreads();
   if (tid == 0) {
     int acc = 0;
@@ -290,7 +299,7 @@ __global__ __launch_bounds__(NT) void trieig_kernel(const double *tri, int n, in
     // (count at the lower end <= index < count at the upper end).
     if (nblk == 1) {
       kid[tid] = sturm_count(sd, se2, 0, n,
-                             gl + (xcut - gl) * (double)(tid + 1) / (double)(NT + 1), sc);
+                             gl + (xcut - gl) * (double)(tid + 1) / (double)(NT + 1));
       __syncthreads();
     }
     // Multisection, G lanes per task over all workgroups (the lanes of a
@@ -320,6 +329,7 @@ __global__ __launch_bounds__(NT) void trieig_kernel(const double *tri, int n, in
       if (lo < NT) c = gl + (xcut - gl) * (double)(lo + 1) / (double)(NT + 1);
       if (lo > 0) a = gl + (xcut - gl) * (double)lo / (double)(NT + 1);
     }
+    if (t - s == 1) a = c = sd[s];
     const int base = lane - sub;   // the group's first lane
     for (int it = 0; it < 160; ++it) {
       // (to eps ||T|| / 2, or no number left between; outer points may already
@@ -329,7 +339,7 @@ __global__ __launch_bounds__(NT) void trieig_kernel(const double *tri, int n, in
       if (!__any(act)) break;
       const double x = a + (c - a) * (double)(sub + 1) / (double)(G + 1);
       const unsigned long long above =
-          __ballot(sturm_count(sd, se2, s, t, x, sc) > loc);
+          __ballot(sturm_count(sd, se2, s, t, x) > loc);
       // first point of the group above the index (G: none)
       const unsigned long long mine = (above >> base) & (G == 64 ? ~0ull : ((1ull << G) - 1));
       const int first = mine ? __builtin_ctzll(mine) : G;
@@ -648,7 +658,7 @@ __global__ __launch_bounds__(NT) void trieig_kernel(const double *tri, int n, in
   }
   if (blockIdx.x == 0)
     for (int task = tid; task < ntask; task += NT)
-      if (tpos[task] < nb) w[tpos[task]] = tlam[task];
+      if (tpos[task] < nb) w[tpos[task]] = __builtin_amdgcn_ldexp(tlam[task], tex);
 }
 
 }  // namespace
