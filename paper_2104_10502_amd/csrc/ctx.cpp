@@ -557,6 +557,10 @@ qeh_status qeh_ctx_create(const qeh_cell *cell, void *arena, size_t arena_bytes,
   c->wide = g.wide;
   c->ldb = g.ldb;
   c->kchunk = g.kchunk;
+  if (c->prec == QEH_FP64) {
+    c->form_proj = cgemm_form(c->block, c->nkb, c->npw, 0);
+    c->form_expand = cgemm_form(c->block, c->npw, c->nkb, 1);
+  }
   c->nchunk = g.nchunk;
   c->dx = g.dx;
   c->dy = g.dy;
@@ -862,6 +866,7 @@ qeh_status apply_block(qeh_ctx *c, int part, int nbk, const double2 *psi, int ld
     g1.nsplit = c->nsplit;
     g1.kchunk = c->kchunk;
     g1.split_stride = (long)c->block * c->nkb;
+    g1.form = c->form_proj;
     g1.rmode = c->gamma ? 1 : 0;   // Gamma: only the real part enters becp
     {
       StageGuard g(c, 3);
@@ -890,6 +895,7 @@ qeh_status apply_block(qeh_ctx *c, int part, int nbk, const double2 *psi, int ld
     g3.accumulate = part == 2 ? 1 : 0;
     g3.nsplit = 1;
     g3.kchunk = c->nkb;
+    g3.form = c->form_expand;
     g3.rmode = c->gamma ? 2 : 0;   // Gamma: ps is real
     g3.tile = c->wide ? 2 : 0;
     {
@@ -964,6 +970,7 @@ qeh_status apply_s_impl(qeh_ctx *c, int nb, const double *psi, int ldpsi, double
     g1.nsplit = c->nsplit;
     g1.kchunk = c->kchunk;
     g1.split_stride = (long)c->block * c->nkb;
+    g1.form = c->form_proj;
     g1.rmode = c->gamma ? 1 : 0;
     g1.tile = c->wide ? 2 : c->gamma ? 1 : 0;
     e = f64 ? launch_cgemm(g1, c->stream) : launch_split_gemm(g1, c->stream);
@@ -986,6 +993,7 @@ qeh_status apply_s_impl(qeh_ctx *c, int nb, const double *psi, int ldpsi, double
     g3.accumulate = 1;
     g3.nsplit = 1;
     g3.kchunk = c->nkb;
+    g3.form = c->form_expand;
     g3.rmode = c->gamma ? 2 : 0;
     g3.tile = c->wide ? 2 : 0;
     e = f64 ? launch_cgemm(g3, c->stream) : launch_split_gemm(g3, c->stream);

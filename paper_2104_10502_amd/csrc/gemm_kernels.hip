@@ -16,7 +16,9 @@
 // the four-product form (Cr = Ar Br - Ai Bi, Ci = Ar Bi + Ai Br), and it issues
 // a quarter fewer MFMAs.  The kernels are held to three waves per SIMD (the
 // third accumulator set would otherwise push them to two).  The flat tiles wait
-// for memory rather than for the MFMAs and take the four-product form (RM = 3).
+// for memory rather than for the MFMAs and take the four-product form (RM = 3);
+// H psi and S psi, whose bits may not depend on how the bands are grouped, take
+// the form of the context's whole block in launches of any number of bands.
 // Two cheaper forms serve the Gamma-point projections (RM = 1: only the real
 // part of C is wanted; RM = 2: A is real, Cr = sum Ar Br and Ci = sum Ar Bi):
 // two MFMA products per step.
@@ -241,9 +243,16 @@ hipError_t run_tile(const GemmDesc &g, hipStream_t s) {
 }
 
 // 64 x 64 tiles with K slices of 8, or 16 x 64 with slices of 16 (cgemm_flat).
+// Both add an element's terms in the order of k, so where the form (the number of
+// real products) is given, the tile changes no bit of the result.  Four products
+// exist on flat tiles only.
 template <int BMODE, int RM> hipError_t run(const GemmDesc &g, hipStream_t s) {
-  if (cgemm_flat(g.M, g.N, g.K, g.bmode))
-    return run_tile<BMODE, RM == 0 ? 3 : RM, 16, 64, 16, 1, 4>(g, s);
+  const bool flat = cgemm_flat(g.M, g.N, g.K, g.bmode);
+  if constexpr (RM == 0) {
+    if (g.form == 4 || (g.form == 0 && flat))
+      return run_tile<BMODE, 3, 16, 64, 16, 1, 4>(g, s);
+  }
+  if (flat) return run_tile<BMODE, RM, 16, 64, 16, 1, 4>(g, s);
   return run_tile<BMODE, RM, 64, 64, 8, 2, 2>(g, s);
 }
 
@@ -372,6 +381,8 @@ bool cgemm_flat(int M, int N, int K, int bmode) {
   if (bmode == 0 ? (double)M * N * K < 5e8 : t64 < 384) return true;
   return 64 * ((M + 63) / 64) > 1.35 * 16 * ((M + 15) / 16);
 }
+
+int cgemm_form(int M, int N, int K, int bmode) { return cgemm_flat(M, N, K, bmode) ? 4 : 3; }
 
 // The Gamma-point forms: RM = 1 for beta^H psi (bmode 0), RM = 2 for beta ps
 // (bmode 1, A = ps real in complex storage).

@@ -122,6 +122,7 @@ struct qeh_ctx {
                         // boxes of the lane-pair / lane-quad sizes
   int stick_path = 0;   // as reported: 1 for single-precision N3 of a lane-pair size
   int nsplit = 1, kchunk = 0;
+  int form_proj = 0, form_expand = 0;   // FP64 beta^H psi and beta ps: GemmDesc::form, by block
   int wide = 0;         // 1: wide single-precision tiles for the projector products
   int ldb = 0;          // row length of beta and psi32 (npw; single precision: padded to
                         // whole 128-byte lines)
@@ -270,12 +271,15 @@ struct GemmDesc {
   int nsplit, kchunk; long split_stride;
   int tile;   // launch_split_gemm: 0 = 64 x 64, 1 = 64 x 128, 2 = 128 x 128
   int rmode;  // 0 complex; 1 only Re(C) wanted (Im written 0); 2 A real (Im A ignored)
+  int form;   // launch_cgemm, complex: 3 or 4 real products (cgemm_form), 0 by this product's size
 };
 // FP64 operands and results.
 hipError_t launch_cgemm(const GemmDesc &g, hipStream_t s);
 // Whether launch_cgemm takes flat 16 x 64 tiles (else 64 x 64): callers that
 // split K count their workgroups by it.
 bool cgemm_flat(int M, int N, int K, int bmode);
+// Real products of a complex one of this size: 4 (flat tiles) or 3.
+int cgemm_form(int M, int N, int K, int bmode);
 // The single-precision projector products: B and the products in single
 // precision, beta^H psi (bmode 0, conjB; A in float or double, C float) and
 // beta ps (bmode 1; C double).
