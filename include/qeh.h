@@ -492,11 +492,16 @@ qeh_status qeh_server_destroy(qeh_server *srv);
  * kernel, on square boxes of some sizes: 2 in the mixed form with N1 = N2 = 16,
  * 18, 20, 24, 30, 32, 36, 40, 48, 50, 54, 60, 64, 72, 80 or 90; 4 in FP64 with 16,
  * 20, 24, 32, 36, 40, 48, 60, 64 or 72 and in the mixed form with 96, 120, 128,
- * 144 or 160),
- * stick path (1 in the mixed form with N3 one of plane path 2's sizes, else 0),
+ * 144 or 160; a name of the size that does not tell which kernel runs),
+ * stick path (1 in the mixed form with N3 one of plane path 2's sizes, else 0;
+ * likewise a name only),
  * projector tiles (0 the 64-row MFMA tiles, 1 the wide single-precision tiles:
- * QEH_MIXED with >= 2048 projectors and a block of >= 128 bands)].  out has
- * room for n values (up to 12).
+ * QEH_MIXED with >= 2048 projectors and a block of >= 128 bands),
+ * plane kernel (0 LDS passes, 1 split through HBM, 2 two-factor),
+ * stick kernels K1 and K3 (0 LDS passes, 1 two-factor),
+ * density kernel that a call now would take (0 LDS-pass rows, 1 lane-pair rows, 2
+ * fused two-factor, -1 none: the box is too large), bands per density
+ * subgroup].  out has room for n values (up to 16).
  * The plane pass takes the two-factor kernel on square planes (N1 = N2) of a
  * compiled size (products of 2, 3, 5 and 7 up to 192 with two factors of at
  * most 16, and 125) whose x-extent columns fit in LDS, else LDS passes of

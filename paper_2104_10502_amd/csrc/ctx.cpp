@@ -346,8 +346,8 @@ void geometry(const qeh_cell *c, const HostMaps &hm, Geometry *g) {
   }
   // two-factor kernel (square planes of a compiled size whose columns fit in
   // LDS): faster than the LDS-pass and the split kernels at every size measured
-  // (1.5 to 4.2 times, 12 .. 180).  Plane paths 2 and 4 are what the reports
-  // call the boxes of the lane-pair and lane-quad sizes.  QEH_PLANE_KERNEL=generic and
+  // (1.5 to 4.2 times, 12 .. 180).  Plane paths 2 and 4 are names of box sizes
+  // (what runs is reported apart).  QEH_PLANE_KERNEL=generic and
   // QEH_FORCE_SPLIT_PLANE=1 keep the LDS-pass kernels (test hooks).
   g->two = TwoGeom{};
   {
@@ -1189,9 +1189,14 @@ qeh_status qeh_ctx_hdiag(const qeh_ctx *c, double *hdiag) {
 
 qeh_status qeh_ctx_info(const qeh_ctx *c, long *out, int n) {
   if (!c || !out) return invalid("null argument");
-  const long v[12] = {c->npw, c->nst, c->nkb, c->n1, c->n2, c->n3, c->ext, c->block, c->prec,
-                      c->plane_path, c->stick_path, c->wide};
-  for (int i = 0; i < n && i < 12; ++i) out[i] = v[i];
+  DensityGeom dg{};
+  const bool density = density_geometry(c, &dg);
+  const long v[16] = {c->npw, c->nst, c->nkb, c->n1, c->n2, c->n3, c->ext, c->block, c->prec,
+                      c->plane_path, c->stick_path, c->wide,
+                      // the kernels that run
+                      c->two.on ? 2 : c->plane_path == 1 ? 1 : 0, c->st2.on,
+                      !density ? -1 : dg.fused ? 2 : dg.pair ? 1 : 0, density ? dg.bsub : 0};
+  for (int i = 0; i < n && i < 16; ++i) out[i] = v[i];
   return QEH_OK;
 }
 

@@ -118,9 +118,9 @@ struct qeh_ctx {
   int has_q = 0;        // 1: overlap q blocks present (S != 1)
   int n1 = 0, n2 = 0, n3 = 0, ext = 0, hmin = 0;
   int block = 0, prec = 0;
-  int plane_path = 0;   // as reported: 0 one kernel, 1 split through HBM; 2, 4: one kernel,
-                        // boxes of the lane-pair / lane-quad sizes
-  int stick_path = 0;   // as reported: 1 for single-precision N3 of a lane-pair size
+  int plane_path = 0;   // 0 one kernel, 1 split through HBM; 2, 4: one kernel, names of box
+                        // sizes only (qeh_ctx_info keeps them); which kernel: two.on
+  int stick_path = 0;   // a name of sizes only as well; which kernel: st2.on
   int nsplit = 1, kchunk = 0;
   int form_proj = 0, form_expand = 0;   // FP64 beta^H psi and beta ps: GemmDesc::form, by block
   int wide = 0;         // 1: wide single-precision tiles for the projector products
