@@ -497,7 +497,8 @@ qeh_status qeh_server_destroy(qeh_server *srv);
  * likewise a name only),
  * projector tiles (0 the 64-row MFMA tiles, 1 the wide single-precision tiles:
  * QEH_MIXED with >= 2048 projectors and a block of >= 128 bands),
- * plane kernel (0 LDS passes, 1 split through HBM, 2 two-factor),
+ * plane kernel (0 LDS passes, 1 split through HBM, 2 two-factor, 3 two-factor
+ * with its columns unpadded in LDS),
  * stick kernels K1 and K3 (0 LDS passes, 1 two-factor),
  * density kernel that a call now would take (0 LDS-pass rows, 1 lane-pair rows, 2
  * fused two-factor, -1 none: the box is too large), bands per density

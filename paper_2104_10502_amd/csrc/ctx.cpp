@@ -344,17 +344,18 @@ void geometry(const qeh_cell *c, const HostMaps &hm, Geometry *g) {
       g->pg.lds_bytes = plane_lds_bytes(prec, hm.ext, n1, n2, g->pg);
     }
   }
-  // two-factor kernel (square planes of a compiled size whose columns fit in
-  // LDS): faster than the LDS-pass and the split kernels at every size measured
-  // (1.5 to 4.2 times, 12 .. 180).  Plane paths 2 and 4 are names of box sizes
-  // (what runs is reported apart).  QEH_PLANE_KERNEL=generic and
-  // QEH_FORCE_SPLIT_PLANE=1 keep the LDS-pass kernels (test hooks).
+  // two-factor kernel on square planes of a compiled size whose columns leave LDS
+  // for enough rows (two_geometry has both sides of that line).  Plane paths 2 and
+  // 4 are names of box sizes (what runs is reported apart).
+  // QEH_PLANE_KERNEL=generic and QEH_FORCE_SPLIT_PLANE=1 keep the LDS-pass kernels
+  // (test hooks).
   g->two = TwoGeom{};
   {
     const char *kern = std::getenv("QEH_PLANE_KERNEL");
     const char *force = std::getenv("QEH_FORCE_SPLIT_PLANE");
     const bool keep = (kern && std::strcmp(kern, "generic") == 0) || (force && force[0] == '1');
-    if (!keep && two_geometry(prec, n1, n2, hm.ext, hm.kmax - hm.kmin + 1, &g->two))
+    if (!keep && two_geometry(prec, n1, n2, hm.ext, hm.kmax - hm.kmin + 1,
+                              g->plane_path == 1, &g->two))
       g->plane_path = pair_plane_supported(prec, n1, n2)   ? 2
                       : quad_plane_supported(prec, n1, n2) ? 4
                                                            : 0;
@@ -1194,7 +1195,7 @@ qeh_status qeh_ctx_info(const qeh_ctx *c, long *out, int n) {
   const long v[16] = {c->npw, c->nst, c->nkb, c->n1, c->n2, c->n3, c->ext, c->block, c->prec,
                       c->plane_path, c->stick_path, c->wide,
                       // the kernels that run
-                      c->two.on ? 2 : c->plane_path == 1 ? 1 : 0, c->st2.on,
+                      c->two.on ? 2 + c->two.tight : c->plane_path == 1 ? 1 : 0, c->st2.on,
                       !density ? -1 : dg.fused ? 2 : dg.pair ? 1 : 0, density ? dg.bsub : 0};
   for (int i = 0; i < n && i < 16; ++i) out[i] = v[i];
   return QEH_OK;

@@ -852,7 +852,7 @@ bool density_geometry(const qeh_ctx *c, DensityGeom *dg) {
   // compiled and its LDS fits
   const bool unfused =
       kern && (std::strcmp(kern, "rows") == 0 || std::strcmp(kern, "generic") == 0);
-  const size_t lds2 = !c->two.on || unfused         ? 0
+  const size_t lds2 = !c->two.on || c->two.tight || unfused ? 0   // (its columns are padded)
                       : c->prec == QEH_FP64 ? density_two_lds_f64(n1, c->ext)
                                             : density_two_lds_f32(n1, c->ext);
   dg->fused = lds2 > 0 && lds2 <= (size_t)kLdsMax;

@@ -68,14 +68,22 @@ constexpr int threads(bool f64, int n) {
 }
 constexpr int pitch_b(int b) { return b | 1; }   // odd: no bank conflicts over k
 constexpr int pitch(int n, int b) { return (n / b * pitch_b(b)) | 1; }
+// Single-precision sizes whose columns can exceed LDS also have a form without
+// that padding (TIGHT), for the extents at which the padded columns leave too
+// little LDS for rows (two_geometry): its bank conflicts cost up to 3% (N = 160, 95
+// columns, 64 bands of 24 planes: 181 and 187 us), more rows at a time give more back
+// (113 columns 423 -> 221 us).
+constexpr bool has_tight(bool f64, int n) {
+  return !f64 && pitch_b(factor_b(n)) != factor_b(n) && 8 * n * pitch(n, factor_b(n)) > kLdsMax;
+}
 
-template <typename C, int N, int B, int NT, bool HALF>
+template <typename C, int N, int B, int NT, bool HALF, bool TIGHT>
 __global__ __launch_bounds__(NT) void k2_two(
     C *__restrict__ sbuf, const typename real_of<C>::type *__restrict__ vs,
     const int *__restrict__ tidx, const C *__restrict__ tw, int nst, int n3, int ext, int rc,
     int nbk, int per_xcd) {
   using R = typename real_of<C>::type;
-  constexpr int A = N / B, BP = pitch_b(B), LD = pitch(N, B);
+  constexpr int A = N / B, BP = TIGHT ? B : pitch_b(B), LD = TIGHT ? N | 1 : pitch(N, B);
   constexpr int AU = HALF ? (A + 1) / 2 : A;   // values of a that hold data
   constexpr int NTA = NT / A * A;              // threads of the (line, k) passes: fixed k
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -229,7 +237,12 @@ template <typename C, int N> hipError_t launch(const qeh_ctx *c, int nbk) {
                        c->n3, c->ext, c->two.rc, nbk, per_xcd);
     return hipGetLastError();
   };
-  return c->two.half ? go(&k2_two<C, N, B, NT, true>) : go(&k2_two<C, N, B, NT, false>);
+  if constexpr (has_tight(sizeof(R) == 8, N))
+    if (c->two.tight)
+      return c->two.half ? go(&k2_two<C, N, B, NT, true, true>)
+                         : go(&k2_two<C, N, B, NT, false, true>);
+  return c->two.half ? go(&k2_two<C, N, B, NT, true, false>)
+                     : go(&k2_two<C, N, B, NT, false, false>);
 }
 
 // Charge density: one workgroup = one z plane of one subgroup of bands, the

@@ -58,10 +58,11 @@ struct SplitGeom {
   FastDiv cg_div, cglast_div, rg_div, rglast_div;
 };
 
-// Two-factor plane kernel (plane2.h): whether it runs, its column pitch, the
-// split of a y position p into slot (p / b) * bp + p % b, rows at a time.
+// Two-factor plane kernel (plane2.h): whether it runs, with unpadded columns or
+// not, its column pitch, the split of a y position p into slot (p / b) * bp + p % b,
+// rows at a time.
 struct TwoGeom {
-  int on, half, rc, ldT, b, bp;
+  int on, tight, half, rc, ldT, b, bp;
   size_t lds;
 };
 
@@ -187,8 +188,8 @@ bool pair_plane_supported(int prec, int n1, int n2);
 bool quad_plane_supported(int prec, int n1, int n2);
 
 // Two-factor plane kernel: geometry for an x-extent of ext columns and a y
-// extent of exty (false: no compiled form, or the columns exceed LDS).
-bool two_geometry(int prec, int n1, int n2, int ext, int exty, TwoGeom *g);
+// extent of exty (false: no compiled form, or the columns leave too little LDS).
+bool two_geometry(int prec, int n1, int n2, int ext, int exty, bool split, TwoGeom *g);
 hipError_t launch_k2_two_f32(const qeh_ctx *c, int nbk);
 hipError_t launch_k2_two_f64(const qeh_ctx *c, int nbk);
 

@@ -14,7 +14,7 @@ from test_gpu_stick_sizes import SIZES as STICK_SIZES, _cell as _stick_cell
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
-LDS, SPLIT, TWO = 0, 1, 2             # plane kernel
+LDS, SPLIT, TWO, TIGHT = 0, 1, 2, 3   # plane kernel
 ROWS, PAIR_ROWS, FUSED = 0, 1, 2      # density kernel
 
 
