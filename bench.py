@@ -54,7 +54,6 @@ MFMA_F64_TFLOPS = 78.6
 VALU_F32_ONE_WIDE_TFLOPS = 78.6
 VALU_F64_TFLOPS = 78.6
 METRIC = "H|psi> band-applies/sec (FFT pts*bands/s) FP32 vs FP64; serve p50/p99 latency"
-DENSITY_BSUB = 16   # bands per density subgroup at most (the library picks 4 to 16)
 
 
 def fft_flops(n):
@@ -88,19 +87,16 @@ def algorithmic(stage, shape, prec, nb):
     npw_fft = 2 * npw - 1 if gam else npw
     if stage == "k1_scatter_zinv":
         # read psi (complex128) and the box map, write the sticks (+ the FP32
-        # psi copy the single-precision beta^H psi reads, complex k only)
-        if gam:
-            return "hbm", nb * 16 * npw + nt * (4 * npw_fft + c * nst * n3)
-        return "hbm", nb * (16 * npw + c * nst * n3 + 4 * npw + (8 * npw if prec else 0))
+        # psi copy the single-precision beta^H psi reads)
+        return "hbm", (nb * (16 * npw + (8 * npw if prec else 0)) +
+                       nt * (4 * npw_fft + c * nst * n3))
     if stage == "k2_plane":
         return "hbm", plane_bytes(shape, prec, nb)
     if stage == "k3_zfwd_gather":
-        if gam:
-            # K3 to the full-sphere pair buffer, then the unpack: read the buffer
-            # at G and -G, psi, |G|^2; write H psi
-            return "hbm", (nt * (c * nst * n3 + 4 * npw_fft + 2 * 16 * npw_fft) +
-                           nb * 2 * 16 * npw + 8 * npw)
-        return "hbm", nb * (c * nst * n3 + 16 * npw + 16 * npw + 4 * npw) + 8 * npw
+        # read the sticks, the box map, psi and |G|^2, write H psi; behind the
+        # LDS-pass z transforms a Gamma pair goes through a full-sphere buffer
+        unpack = nt * 2 * 16 * npw_fft if gam and not shape["stick_kernel"] else 0
+        return "hbm", nt * (c * nst * n3 + 4 * npw_fft) + unpack + nb * 2 * 16 * npw + 8 * npw
     if stage in ("calbec_gemm", "addnl_gemm"):
         # complex: 8 flops per complex multiply-add; Gamma: real products over
         # the half sphere, 2 x (2 flops) per stored coefficient
@@ -108,11 +104,13 @@ def algorithmic(stage, shape, prec, nb):
     if stage == "dscale":
         return "hbm", nb * nkb * c * 2
     ext = shape["ext"]
-    nsub = -(-nb // DENSITY_BSUB)
+    nsub = -(-nb // shape["density_bands"])   # the library's subgroups of bands
     if stage == "density_columns":   # read sticks, write inverse-y columns
         return "hbm", nb * c * (nst * n3 + ext * n2 * n3)
-    if stage == "density_rows":      # read the columns, write the subgroup partial planes
-        return "hbm", nb * c * ext * n2 * n3 + 8 * nsub * nfft
+    if stage == "density_rows":
+        # read the columns (fused pass: the sticks), write the subgroup partial planes
+        fused = shape["density_kernel"] == 2
+        return "hbm", nb * c * (nst if fused else ext * n2) * n3 + 8 * nsub * nfft
     if stage == "density_reduce":    # read the partial planes, write rho
         return "hbm", 8 * nsub * nfft + 8 * nfft
     raise KeyError(stage)
@@ -128,10 +126,9 @@ def plane_bytes(shape, prec, nb):
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hpsi_c5_gamma_hbm_traffic.json")
 
 
-# sources of the H|psi> kernels whose HBM counters are stored (the FFT
-# passes, the projector GEMMs and D scaling, the Gamma unpack) and the headers
-# they include
-HPSI_SOURCES = ("cplx.h", "dav_kernels.hip", "fft_kernels.hip", "fft_reg.h", "gemm_kernels.hip",
+# sources of the H|psi> kernels whose HBM counters are stored (the transforms,
+# the projector GEMMs and D scaling) and the headers they include
+HPSI_SOURCES = ("cplx.h", "fft_kernels.hip", "fft_radix.h", "fft_reg.h", "gemm_kernels.hip",
                 "plane2.h", "plane2_f32.hip", "plane2_f64.hip", "qeh_internal.h", "split_gemm.hip",
                 "stick2.h", "stick2_f32.hip", "stick2_f64.hip")
 
