@@ -584,12 +584,24 @@ __global__ __launch_bounds__(kRT) __attribute__((amdgpu_waves_per_eu(2))) void k
 }
 
 // rho[i] = (accumulate ? rho[i] : 0) + scale * sum_sub partial[sub][i], sub in order.
+// Bound on small planes: the latency of a point's loads, which one after another cost
+// more than the subgroups of 4 bands save (256 bands on 24^2 x 32, mixed, 64
+// subgroups: rows 18 and reduction 19 us; 8 loads in flight 18 and 7; subgroups of
+// 16 on lane pairs 20 and 13).
 __global__ __launch_bounds__(256) void density_reduce(const double *__restrict__ partial,
                                                       int nsub, long npts, double scale,
                                                       double *__restrict__ rho, int accumulate) {
   for (long i = blockIdx.x * 256L + threadIdx.x; i < npts; i += (long)gridDim.x * 256) {
     double t = 0.0;
-    for (int s = 0; s < nsub; ++s) t += partial[(size_t)s * npts + i];
+    int s = 0;
+    for (; s + 8 <= nsub; s += 8) {
+      double v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = partial[(size_t)(s + u) * npts + i];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) t += v[u];
+    }
+    for (; s < nsub; ++s) t += partial[(size_t)s * npts + i];
     rho[i] = (accumulate ? rho[i] : 0.0) + scale * t;
   }
 }
