@@ -504,9 +504,9 @@ qeh_status qeh_server_destroy(qeh_server *srv);
  * fused two-factor, -1 none: the box is too large), bands per density
  * subgroup].  out has room for n values (up to 16).
  * The plane pass takes the two-factor kernel on square planes (N1 = N2) of a
- * compiled size (products of 2, 3, 5 and 7 up to 192 with two factors of at
- * most 16, and 125) whose x-extent columns fit in LDS, else LDS passes of
- * small radices.  Environment variables read by qeh_ctx_plan / qeh_ctx_create:
+ * compiled size (products of 2, 3, 5 and 7 from 12 to 192 with two factors of at
+ * most 16, without 49 and 98, and 125) whose x-extent columns leave LDS for enough
+ * rows, else LDS passes of small radices or the split kernel.  Environment variables read by qeh_ctx_plan / qeh_ctx_create:
  * QEH_FORCE_SPLIT_PLANE=1 forces the split path (a test hook);
  * QEH_STICK_KERNEL=generic keeps the LDS-pass z transforms where the two-factor
  * ones would run (N3 a compiled size; a test hook);

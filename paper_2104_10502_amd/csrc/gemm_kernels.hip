@@ -52,9 +52,9 @@ __device__ __forceinline__ void mfma(double a, double b, doublex4 &c) {
 // Bound: the f64 matrix rate (72.7 TFLOP/s for a library product of 8192^3
 // here, 62 for this kernel on 2048 x 2048 x 4096) and, at Gamma, beta from HBM
 // (2.4 GB at 2048 projectors: 0.5 ms).  Planar LDS tiles with masked loads ->
-// this kernel (us): 128 x 512, K 23 976, 197 -> 177; 128 x 23 976, K 512,
-// 196 -> 177; Gamma 64 x 2 048, K 74 047, 791 -> 731; 64 x 74 047, K 2 048,
-// 890 -> 768.
+// this kernel (us, kernel traces of H psi): 128 x 512, K 23 976, 199 -> 185;
+// 128 x 23 976, K 512, 209 -> 195; Gamma 64 x 2 048, K 74 047, 828 -> 776;
+// 64 x 74 047, K 2 048, 913 -> 837.
 template <int BMODE, int BM, int BN, int BK, int RM, int WGM, int WGN, bool CJ>
 __global__ __launch_bounds__(64 * WGM * WGN) __attribute__((amdgpu_waves_per_eu(3)))
 void cgemm_kernel(

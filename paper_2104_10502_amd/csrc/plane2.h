@@ -29,13 +29,18 @@
 // Bound: vector issue (about 30 lane operations a point and transform, twice
 // the 5 n log2 n count's share of the FMA rate) and, where one workgroup of
 // columns fills a CU's LDS, the latency of its passes between barriers.
-// Measured per launch, the kernels it replaced (lane pairs, quads or octets
-// with DPP exchanges, or LDS passes of radix 2 to 8) -> this one:
-//   FP32  45^3, 202 bands            182 ->  49 us    FP64  45^3, 64   104 ->  36
-//         72^3, 128 bands            175 -> 134             72^3, 128  349 -> 288
-//         135^3, 32 band pairs       871 -> 255             135^3, 32 2384 -> 660
-//         160 x 160 x 168, 64 pairs 1488 -> 819
-// and 1.0 to 4.2 times faster at every compiled size from 12 to 180 measured.
+// Measured per launch inside H psi (kernel traces of the same card), the kernel it
+// replaced (LDS passes of radix 2 to 8; * lane pairs, quads or octets with DPP
+// exchanges) -> this one:
+//   FP32  45^3, 202 bands            186 ->   54 us    FP64  30^3, 16    16 ->   9
+//         72^3, 128 bands            176* -> 139             72^3, 128  360* -> 287
+//         135^3, 32 band pairs       874 ->  296             135^3, 32 2434 ->  752
+//         160 x 160 x 168, 64 pairs 1493* -> 1015
+// The plane pass alone, without the matrix products before it, runs at a higher
+// clock: 135^3 FP32 880 -> 263, the last line 1471* -> 822.  At half-filled lines of
+// all compiled sizes (64 bands): 1.5 to 6.7 times as fast as the LDS passes, 1.0
+// to 1.4 as the lane pairs (16 sizes), 1.3 to 1.5 as the quads in FP64 (10) and 1.5 to
+// 1.8 as quads and octets in FP32 (5); FP64 lines above 135 points do not fit.
 #pragma once
 
 #include <algorithm>
@@ -58,9 +63,9 @@ constexpr int factor_b(int n) {
 }
 // Threads per workgroup: about two of a plane's row items ((row, k) and
 // (row, b)) per thread and pass at the smaller sizes; the large single-precision
-// planes leave room for one workgroup per CU and take 1024 (N = 160: 819 us per
-// 64 band pairs of 168 planes, 1061 with 512; N = 72: 256 and 512 within 1%),
-// the FP64 ones 512 (1024 would spill).
+// planes leave room for one workgroup per CU and take 1024 (the plane pass alone,
+// N = 160, 64 band pairs of 168 planes: 822 us, 1040 with 512; 135, 32 pairs of 135:
+// 263 and 327; N = 72: 256 and 512 within 1%), the FP64 ones 512 (1024 would spill).
 constexpr int threads(bool f64, int n) {
   return n <= 36 ? 128
          : n <= (f64 ? 60 : 72) ? 256
@@ -250,7 +255,7 @@ template <typename C, int N> hipError_t launch(const qeh_ctx *c, int nbk) {
 // holds each point's f_b |psi_b|^2 sums in registers, in band order: a thread
 // meets the same (row, k) items for every band (NCH chunks of RC rows, unrolled;
 // the y and x shifts are unit-modulus phases of psi).  Bound: as the plane pass.
-// 72^3, FP64, 128 bands: 261 us on lane quads -> 182.  Whole density of 64 bands
+// 72^3, FP64, 128 bands: 266 us on lane quads -> 184.  Whole density of 64 bands
 // on lane quads (FP64) or pairs, or separate column and row passes (*) -> this
 // kernel (us):
 //   FP64  45^3 172* -> 66   60^3 131 -> 96   80^3 423* -> 172   120^2 x 48 519* -> 251
@@ -423,7 +428,8 @@ hipError_t launch_density(const qeh_ctx *c, int nbk, int bsub, const double *occ
   }
 }
 
-// Sizes compiled: products of 2, 3, 5, 7 up to 192 with both factors <= 16, and 125.
+// The 49 sizes compiled: products of 2, 3, 5, 7 up to 192 with both factors <= 16,
+// without 49 and 98, and 125.
 #define QEH_TWO_SIZES(X)                                                                       \
   X(12) X(14) X(15) X(16) X(18) X(20) X(21) X(24) X(25) X(27) X(28) X(30) X(32) X(35) X(36)    \
   X(40) X(42) X(45) X(48) X(50) X(54) X(56) X(60) X(63) X(64) X(70) X(72) X(75) X(80) X(81)    \

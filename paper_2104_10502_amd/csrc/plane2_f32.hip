@@ -18,8 +18,8 @@ namespace {
 // Rows rc at a time, from the LDS left by the columns: as many workgroups per
 // CU as their registers allow (20 waves in single precision, 12 in FP64), fewer
 // where a pass over rc rows would then leave most threads idle.  N = 72 in
-// single precision: 36 rows (35 KB) 134 us per 128 bands, 7 rows (26 KB) 276;
-// N = 160: 80 rows 819 us, 14 rows 1 480.
+// single precision, alone: 36 rows (35 KB) 134 us per 128 bands, 7 rows (26 KB) 276;
+// N = 160, 64 band pairs: 80 rows 819 us, 14 rows 1 480.
 bool rows_geometry(bool f64, int n, int ext, bool tight, TwoGeom *g) {
   const int b = plane2::factor_b(n), a = n / b, nt = plane2::threads(f64, n);
   const size_t cs = f64 ? 16 : 8;

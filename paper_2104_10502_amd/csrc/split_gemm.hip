@@ -5,7 +5,8 @@
 //
 // Each FP32 operand value x is written as x = x0 + x1 + x2 with bf16 parts
 // (round to nearest, remainders exact in FP32): 3 x 8 bits carry the 24-bit
-// significand.  A product is the six part products whose size is at least
+// significand.  (Values above 3.396e38, the top 0.2% of the float range, round to
+// an infinite first part.)  A product is the six part products whose size is at least
 // 2^-17 of the whole, x0 y0 + x0 y1 + x1 y0 + x1 y1 + x0 y2 + x2 y0, each exact
 // and accumulated in FP32 by the MFMA; the three left out are below 2^-24.
 // The bf16 unit runs 16 times the FP32 one's rate, so six products leave it
@@ -30,13 +31,14 @@
 // products) and, at Gamma, which does half the MFMA work per staged value, the
 // splitting.  Measured, FP32 MFMA kernel (16 x 16 x 4 or 32 x 32 x 2) -> this
 // one, beta^H psi / beta ps:
-//   202 bands x 404 projectors, 5 614 plane waves    48 -> 32 / 68 -> 43 us
-//   128 x 512, 23 976                               108 -> 70 / 119 -> 78 us
-//   64 x 2048, 74 047, Gamma                        508 -> 275 / 555 -> 345 us
-//   128 x 6144, 93 225, Gamma                  2.87 -> 2.15 / 2.95 -> 2.06 ms
-// and against FP64 products of the same FP32 inputs the relative error of
-// beta^H psi fell from 5.0e-7 to 1.8e-7 (128 x 512) and from 1.2e-6 to 6.0e-7
-// (128 x 6144), of beta ps from 5.8e-7 to 4.9e-7 and 1.4e-6 to 1.2e-6.
+//   202 bands x 404 projectors, 5 614 plane waves    58 -> 42 / 68 -> 43 us
+//   128 x 512, 23 976                               109 -> 71 / 124 -> 83 us
+//   64 x 2048, 74 047, Gamma                        443 -> 282 / 482 -> 351 us
+//   128 x 6144, 93 225, Gamma                  2.77 -> 1.62 / 2.82 -> 1.70 ms
+// (kernel traces of H psi on one card); against FP64 products of the same FP32
+// inputs the relative error of beta^H psi fell from 5.0e-7 to 1.8e-7 (128 x 512) and
+// from 1.2e-6 to 6.0e-7 (128 x 6144), of beta ps from 5.8e-7 to 4.9e-7 and 1.4e-6 to
+// 1.2e-6.
 #include <algorithm>
 #include <type_traits>
 

@@ -12,16 +12,18 @@
 // quarter of a line at either end: only the values a < AL and a >= A - AH are
 // cleared, loaded by the first K1 pass and stored by the last K3 pass (HALF).
 //
-// Bound: HBM (psi, the stick buffer, H psi; 4.9 TB/s for K1 of the last line).
+// Bound: HBM (psi, the stick buffer, H psi: 684 MB for K1 of the last line by the
+// counters, 3.9 TB/s; a copy reaches 4.9).
 // Measured, LDS passes of radix 2 to 8 (* lane pairs; Gamma: with the kernel
-// that separated K3's pairs) -> this kernel, K1, K3 (us):
-//   FP64  30, 16 bands          7.7,   9.4 ->   4.4,   4.1
-//         72, 128 bands        57.9,  65.5 ->  40.9,  46.4
-//         135, 32 Gamma pairs   115,   159 ->    80,    89
-//   FP32  45, 202 bands        17.6,  18.4 ->  13.7,  13.5
-//         72, 128 bands *      32.7,  39.3 ->  33.9,  32.5
-//         135, 32 Gamma pairs  98.9,   130 ->    65,    63
-//         168, 64 Gamma pairs   242,   352 ->   179,   165
+// that separated K3's pairs) -> this kernel, K1, K3 (us; kernel traces of H psi):
+//   FP64  30, 16 bands          7.9,   9.1 ->   4.0,   3.7
+//         72, 128 bands        57.8,  66.4 ->  40.4,  46.2
+//         135, 32 Gamma pairs   118,   155 ->    78,    88
+//   FP32  45, 202 bands        17.9,  18.1 ->  13.1,  13.5
+//         72, 128 bands *      32.7,  36.7 ->  33.2,  33.1
+//         135, 32 Gamma pairs  92.9,   125 ->    63,    63
+//         168, 64 Gamma pairs   206,   336 ->   176,   164
+// (K1 of 72 points alone is as fast as it was on lane pairs.)
 #pragma once
 
 #include <algorithm>
