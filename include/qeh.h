@@ -166,7 +166,9 @@ qeh_status qeh_ctx_destroy(qeh_ctx *ctx);
  * psi and hpsi are DEVICE pointers (complex, rows of length npw with leading
  * dimensions ldpsi, ldh >= npw, in complex elements); they must not overlap.
  * Enqueued on the context stream in launches of `block` bands; returns
- * without waiting.  Result is independent of how bands are grouped. */
+ * without waiting.  Result is independent of how bands are grouped, bit for bit
+ * (Gamma contexts: into groups of whole pairs; the bands of a pair share a
+ * transform, and a band's last bits depend on its partner). */
 qeh_status qeh_apply_h(qeh_ctx *ctx, int nb, const double *psi, int ldpsi,
                        double *hpsi, int ldh);
 
